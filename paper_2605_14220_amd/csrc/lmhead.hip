@@ -383,17 +383,50 @@ __global__ __launch_bounds__(256) void lmhead_merge_quad(const Partial* __restri
                                                 row, logp, ent, lse);
 }
 
-// SPLITK4 engine: one thread per row, partials folded left to right.
+// SPLITK4 engine: partials folded left to right, kFoldRows rows per workgroup.
+// The fold is a serial chain of n_vt merges per row, so it is bound by that
+// chain's latency once the partials are at hand: the workgroup brings them in
+// chunks of kFoldTiles per row into LDS with coalesced loads, the next chunk's
+// loads in flight while the first kFoldRows lanes fold the current one. With a
+// thread per row loading its own partials, 2048 rows of 594 took 302 us.
+constexpr int kFoldRows = 16;
+constexpr int kFoldTiles = 64;
 __global__ __launch_bounds__(256) void lmhead_merge_fold(const Partial* __restrict__ part,
                                                          const int32_t* __restrict__ tokens,
                                                          int64_t rows, int n_vt, int V, float* logp,
                                                          float* ent, float* lse) {
-  const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (row >= rows) return;
-  const Partial* p = part + row * n_vt;
-  MSU v = MSU{p[0].m, p[0].s, p[0].u};
-  for (int jt = 1; jt < n_vt; ++jt) v = merge2(v, MSU{p[jt].m, p[jt].s, p[jt].u});
-  finish_row<kVocabTile>(v, p, tokens[row], V, row, logp, ent, lse);
+  constexpr int kLoads = kFoldRows * kFoldTiles / 256;
+  // one partial of padding per row: the folding lanes' rows fall on different banks
+  __shared__ float4 buf[kFoldRows][kFoldTiles + 1];
+  const int64_t row0 = (int64_t)blockIdx.x * kFoldRows;
+  const int tid = threadIdx.x;
+  float4 next[kLoads];
+  auto fetch = [&](int first) {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int r = (tid + 256 * i) / kFoldTiles, jt = first + (tid + 256 * i) % kFoldTiles;
+      next[i] = float4{};  // past the row's tiles: not folded
+      if (row0 + r < rows && jt < n_vt) next[i] = ((const float4*)part)[(row0 + r) * n_vt + jt];
+    }
+  };
+  MSU v = MSU{kNegInf, 0.f, 0.f};
+  fetch(0);
+  for (int first = 0; first < n_vt; first += kFoldTiles) {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) buf[(tid + 256 * i) / kFoldTiles][(tid + 256 * i) % kFoldTiles] = next[i];
+    __syncthreads();
+    if (first + kFoldTiles < n_vt) fetch(first + kFoldTiles);
+    if (tid < kFoldRows) {
+      auto leaf = [&](int i) { const float4 q = buf[tid][i]; return MSU{q.x, q.y, q.z}; };
+      v = first == 0 ? leaf(0) : merge2(v, leaf(0));
+      const int n = n_vt - first < kFoldTiles ? n_vt - first : kFoldTiles;
+#pragma unroll 8
+      for (int i = 1; i < n; ++i) v = merge2(v, leaf(i));
+    }
+    __syncthreads();
+  }
+  const int64_t row = row0 + tid;
+  if (tid < kFoldRows && row < rows) finish_row<kVocabTile>(v, part + row * n_vt, tokens[row], V, row, logp, ent, lse);
 }
 
 }  // namespace
@@ -420,8 +453,17 @@ static hipError_t launch_partials_t(const LmHeadArgs& a, bool persistent, hipStr
 
 hipError_t launch_partials(const LmHeadArgs& a, int rows_per_wg, bool splitk4, hipStream_t s) {
   const bool dump = a.logits != nullptr;
-  if (splitk4)  // a second accumulator set: 64-row tiles of 4 waves
-    return dump ? launch_partials_t<1, 2, true, true>(a, false, s) : launch_partials_t<1, 2, true, false>(a, false, s);
+  if (splitk4) {
+    // A second accumulator set, so waves of 128 x 32 (64 + 64 accumulators per lane). Eight of them on a 128-row
+    // tile put two on each SIMD; it is bound by the LDS operand reads, 10 KB per 16 MFMAs of a wave. Per 2048 rows
+    // at d = 4096, V = 151936: 2.55 ms (1.0 PFLOP/s); four waves on a 64-row tile, one per SIMD, 4.13 ms; four of
+    // 128 x 64 on a 128-row tile 3.65 ms. The 64-row tile stays for calls of at most 64 rows and where its tiles
+    // all fit the chip at once, where fewer, larger ones would leave CUs idle.
+    if (dump) return launch_partials_t<1, 2, true, true>(a, false, s);
+    const int64_t tiles64 = (a.rows + 63) / 64 * n_vocab_tiles(a.V);
+    return rows_per_wg <= 64 || tiles64 <= device_cu_count() ? launch_partials_t<1, 2, true, false>(a, false, s)
+                                                             : launch_partials_t<1, 4, true, false>(a, true, s);
+  }
   switch (rows_per_wg) {
     case 64: return dump ? launch_partials_t<1, 2, false, true>(a, false, s) : launch_partials_t<1, 2, false, false>(a, false, s);
     case 128: return dump ? launch_partials_t<2, 2, false, true>(a, false, s) : launch_partials_t<2, 2, false, false>(a, false, s);
@@ -500,7 +542,8 @@ static hipError_t launch_merge_tree(const Partial* part, const int32_t* tokens, 
 hipError_t launch_merge(const Partial* part, const int32_t* tokens, int64_t rows, int V,
                         bool left_fold, float* logp, float* entropy, float* lse, hipStream_t s) {
   if (left_fold) {
-    const int64_t nb = (rows + 255) / 256;
+    const int64_t nb = (rows + kFoldRows - 1) / kFoldRows;
+    if (nb > 0x7fffffff) return hipErrorInvalidValue;
     hipLaunchKernelGGL(lmhead_merge_fold, dim3((unsigned)nb), dim3(256), 0, s, part, tokens, rows,
                        n_vocab_tiles(V), V, logp, entropy, lse);
     return hipGetLastError();

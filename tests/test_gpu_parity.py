@@ -202,6 +202,27 @@ def test_splitk4_engine_matches_oracle_but_not_bits():
     check_close("splitk4 logits", zb.flatten(), za.double().cpu().flatten(), 1e-4)
 
 
+@pytest.mark.parametrize("T,d,V", [
+    (65, 256, 300 * 256),       # one row past the 64-row tile
+    (128, 512, 128 * 256 + 1),  # a full 128-row tile; two whole fold chunks of 64 tiles and a one-entry tile
+    (131, 256, 150 * 256 - 9),  # a ragged second row tile
+    (300, 256, 64 * 256),       # the fold ends on a chunk
+])
+def test_splitk4_row_tiles_agree(T, d, V):
+    """The split-K4 engine's 128-row tiles against its 64-row ones (micro-batches of 64), bit for bit, and every row
+    against the oracle: the row tile and the fold's chunks change no arithmetic."""
+    print(f"case splitk4 T={T} d={d} V={V}", flush=True)
+    h, W = inputs(T, d, V, seed=T + V)
+    tok = random_tokens(T, V, seed=T)
+    one = tim.logprobs(h, W, tok, 0.8, order=Order.SPLITK4, lse=True)
+    small = tim.logprobs(h, W, tok, 0.8, order=Order.SPLITK4, lse=True, micro_batch=64)
+    for x, y in zip(one, small):
+        assert bits_equal(x, y)
+    ref_lp, ref_H = oracle_rows(h, W, tok, 0.8)
+    check_close("splitk4 logp", one[0], ref_lp, TOL_LOGP)
+    check_close("splitk4 entropy", one[1], ref_H, TOL_ENT)
+
+
 @pytest.mark.parametrize("V,mode", [(4096, Mode.TRAINING), (1000, Mode.TRAINING), (4096, Mode.ROLLOUT),
                                     (151936, Mode.ROLLOUT)])
 def test_duplicated_vocabulary_shifts_by_log2(V, mode):
