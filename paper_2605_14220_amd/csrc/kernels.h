@@ -59,7 +59,8 @@ struct DlogitsArgs {
 // (tilepass.h) over whole 256-row tiles (rows padded up to a multiple of 256,
 // the padding's outputs never written), in 64-deep stage blocks or, with
 // deep, 32-deep ones (then K >= 256); K a multiple of 128, a_rows a multiple
-// of 4. Both forms give the same bits.
+// of 4. The 64-deep form takes smaller output tiles where 256 x 256 ones would
+// leave CUs idle. All forms give the same bits.
 struct GemmArgs {
   const void* a;
   const void* b;

@@ -35,6 +35,8 @@
 // zeros, which add exactly nothing; padding rows only reach outputs that are
 // never written.
 
+#include <algorithm>
+
 #include "tilepass.h"
 
 namespace tim {
@@ -279,6 +281,14 @@ void gemm_nt_f32_deep(GemmArgs a, int n_vt, int n_tt) {
   tile_pass_deep<NTB, WT, kDeepBufs, EpiStore>(a, n_vt, n_tt);
 }
 
+// The product in small output tiles (tile_pass_small), for calls with too few
+// 256 x 256 ones; launch_gemm picks the tile.
+template <int NV, int WT, int NA, int NB>
+__global__ __launch_bounds__(64 * NV * WT)
+void gemm_nt_f32_small(GemmArgs a, int n_at, int n_bt) {
+  tile_pass_small<NV, WT, NA, NB>(a, n_at, n_bt);
+}
+
 // 64 x 64 bf16 tile per workgroup: 16-byte row loads into LDS, then each
 // thread gathers 8 consecutive source rows of one column into one 16-byte
 // store of the destination row, which is packed [C_pad, R_pad] (K = R_pad) in
@@ -357,8 +367,40 @@ hipError_t launch_dlogits(const DlogitsArgs& a, hipStream_t s) {
   return launch_pass<EpiDlogits, 2, 4>(lmhead_dlogits<2, 4>, a, a.V, a.rows, s);
 }
 
+template <int NV, int WT, int NA, int NB>
+static hipError_t launch_small(const GemmArgs& a, hipStream_t s) {
+  using ST = SmallTile<NV, WT, NA, NB>;
+  const int64_t n_at = (a.a_rows + ST::TA - 1) / ST::TA, n_bt = (a.b_rows + ST::BT - 1) / ST::BT;
+  if (n_at * n_bt > 0x7fffffff) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((gemm_nt_f32_small<NV, WT, NA, NB>), dim3((unsigned)(n_at * n_bt)), dim3(64 * ST::NW), 0, s, a,
+                     (int)n_at, (int)n_bt);
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.b_rows <= 0 || a.a_rows <= 0) return hipSuccess;
+  if (!a.deep && !a.accumulate) {
+    // The output tile whose rounds over the chip take the least time: the tiles dealt to the CUs, times what one
+    // round of them costs against a round of 256 x 256 tiles (measured at K = 152064: 3.35 ms; 128 x 256 1.95,
+    // 128 x 128 1.25, 64 x 128 0.83, 64 x 64 0.5 ms a round). The smaller the tile the more LDS and cache traffic
+    // per flop, so smaller ones only win where larger ones leave CUs idle. grad_hidden at K = 152064: 1001 rows at
+    // d = 2048 3.07 ms on 32 tiles of 256 x 256, 0.67 on 256 of 64 x 128; 2000 rows at d = 4096 3.1 ms on 128 tiles,
+    // 1.95 on 256 of 128 x 256; 3000 rows there stay on 192 tiles of 256 x 256 (2 rounds of 128 x 256 cost more).
+    const int64_t cus = device_cu_count();
+    auto cost = [&](int64_t ta, int64_t bt, int64_t round) {
+      const int64_t tiles = ((a.a_rows + ta - 1) / ta) * ((a.b_rows + bt - 1) / bt);
+      return cus > 0 ? (tiles + cus - 1) / cus * round : round;
+    };
+    const int64_t c256 = cost(256, 256, 100), c128w = cost(128, 256, 58), c128 = cost(128, 128, 37),
+                  c64w = cost(64, 128, 24), c64 = cost(64, 64, 15);
+    const int64_t best = std::min({c256, c128w, c128, c64w, c64});
+    if (cus > 0 && best < c256) {
+      if (best == c128w) return launch_small<2, 4, 4, 4>(a, s);
+      if (best == c128) return launch_small<2, 4, 4, 2>(a, s);
+      if (best == c64w) return launch_small<2, 4, 2, 2>(a, s);
+      return launch_small<2, 2, 2, 2>(a, s);
+    }
+  }
   if (a.deep) {  // 32-deep stages: a multiple of 4 of them, at least kDeepBufs + 1
     if (a.K % 128 != 0 || a.K / 32 < kDeepBufs + 1) return hipErrorInvalidValue;
     return launch_pass<EpiStore, 2, 4>(gemm_nt_f32_deep<2, 4>, a, a.a_rows, a.b_rows, s);

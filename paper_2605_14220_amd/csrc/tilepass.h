@@ -45,6 +45,7 @@ struct rsrc_t {
 constexpr int kMaxNBuf = 2;     // LDS stage buffers per workgroup (a power of two, as many as fit up to this)
 constexpr int kGroupV = 4;      // vocab tiles per group in the LM head's workgroup -> tile order
 constexpr int kStoreGroup = 8;  // A tiles per group in the tile order of the plain products
+constexpr int kGroupSmall = 4;  // and of their small tiles
 
 constexpr int kKS = 64;                  // hidden-dimension elements per LDS stage
 constexpr int kRowBytes = kKS * 2;       // bytes of one row in one stage
@@ -787,6 +788,149 @@ __device__ __forceinline__ void tile_pass_deep(const typename E::Args& a, int n_
     cur = make_tile<NTB, WT, E::kGroupA, 2, true>(ops, next_lid, n_vt, n_tt);
   }
   wait_vmem<0>();  // no global->LDS request may outlive the workgroup
+}
+
+// Small output tiles over packed operands (64-deep blocks), for products with
+// too few 256 x 256 tiles to fill the chip. The arithmetic is tile_pass's --
+// the same MFMA, operands per lane and ascending k-steps, so the same bits. A
+// wave holds NA x NB blocks of 16 x 16, a workgroup NV x WT waves: an output
+// tile of TA x BT, both dividing 256, so a tile reads a run of whole rows of
+// its operands' packed blocks. One tile per workgroup and one workgroup per CU,
+// its LDS holding as many 64-deep stages as fit, to cover the cache latency of
+// the few KB a stage brings. What bounds it is the LDS: a stage moves (TA + BT)
+// * 128 bytes in and 2 (NA + NB) KB out per wave, and the measured rounds sit
+// at about 128 bytes per cycle for all four shapes used (128 x 256: 176 KB in
+// 820 ns; 64 x 128: 88 KB in 350 ns). Eight waves of fewer blocks were faster
+// than four of more (128 x 128: 1.25 against 1.45 ms at K = 152064), which
+// leave one wave per SIMD and nothing to issue while it waits.
+template <int NV, int WT, int NA, int NB>
+struct SmallTile {
+  static constexpr int NW = NV * WT;
+  static constexpr int TA = NV * NA * 16;
+  static constexpr int BT = WT * NB * 16;
+  static constexpr int SB = (TA + BT) * kRowBytes;
+  static constexpr int NBUF = 160 * 1024 / SB;
+  static constexpr int LA = TA / (8 * NW);  // 1 KB DMA loads per wave per stage, A
+  static constexpr int LB = BT / (8 * NW);  // and B
+  static constexpr int L = LA + LB;
+  static_assert(kPackRows % TA == 0 && kPackRows % BT == 0, "a tile lies within one packed block row");
+  static_assert(LA * 8 * NW == TA && LB * 8 * NW == BT, "the waves share the loads evenly");
+};
+
+// Load q of a wave's stage request, A blocks first.
+template <class ST>
+__device__ __forceinline__ void small_load(unsigned char* buf, rsrc_t ar, rsrc_t br, int wave, int lane, int soff, int q) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if (q < ST::LA) {
+    const int blk = wave * ST::LA + q;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(ar, (lds_void*)(buf + blk * 1024), 16, (uint32_t)(blk * 64 + lane) * 16u,
+                                             soff, 0, 0);
+  } else {
+    const int blk = wave * ST::LB + (q - ST::LA);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(br, (lds_void*)(buf + ST::TA * kRowBytes + blk * 1024), 16,
+                                             (uint32_t)(blk * 64 + lane) * 16u, soff, 0, 0);
+  }
+#endif
+}
+
+// One k-step: the MFMAs of parity P's operands, one scheduling unit each, with
+// the reads of k-step `rs` of `rb` into the other parity's set and (LOAD) the
+// stage request into `lb` spread over the units.
+template <class ST, int NA, int NB, int P, bool LOAD>
+__device__ __forceinline__ void small_kstep(bf16x8 (&fa)[2][NA], bf16x8 (&fb)[2][NB], f32x4 (&acc)[NA][NB],
+                                            unsigned char* lb, rsrc_t ar, rsrc_t br, int soff, const unsigned char* rb,
+                                            int rs, int wave, int wv, int wt, int lane) {
+  constexpr int NM = NA * NB, NR = NA + NB;
+#pragma unroll
+  for (int i = 0; i < NM; ++i) {
+    const int bi = i / NB, bj = i % NB;
+    acc[bi][bj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[P][bi], fb[P][bj], acc[bi][bj], 0, 0, 0);
+#pragma unroll
+    for (int r = i * NR / NM; r < (i + 1) * NR / NM; ++r) {  // b0 .. b[NB-1], a0 .. a[NA-1]
+      if (r < NB) fb[P ^ 1][r] = read_operand(rb + ST::TA * kRowBytes, (wt * NB + r) * 16 + (lane & 15), rs, lane);
+      else fa[P ^ 1][r - NB] = read_operand(rb, (wv * NA + r - NB) * 16 + (lane & 15), rs, lane);
+    }
+    if constexpr (LOAD) {
+#pragma unroll
+      for (int q = i * ST::L / NM; q < (i + 1) * ST::L / NM; ++q) small_load<ST>(lb, ar, br, wave, lane, soff, q);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// out[j * ldo + i] = sum_k A[i][k] B[j][k] of one TA x BT tile (GemmArgs, never accumulating).
+template <int NV, int WT, int NA, int NB>
+__device__ __forceinline__ void tile_pass_small(const GemmArgs& a, int n_at, int n_bt) {
+  using ST = SmallTile<NV, WT, NA, NB>;
+  constexpr int SB = ST::SB, NBUF = ST::NBUF, L = ST::L;
+  constexpr int kStep = kPackRows * kRowBytes;  // from one packed block to the next
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[NBUF * SB];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wv = wave % NV, wt = wave / NV;
+  const int lane = threadIdx.x & 63;
+
+  // logical tile id: contiguous ranges per XCD, in the grouped order of tile_of_lid
+  const int n_tiles = n_at * n_bt;
+  const int x = blockIdx.x & 7, tq = n_tiles >> 3, trm = n_tiles & 7;
+  int ai, bi_t;
+  tile_of_lid<kGroupSmall>(x * tq + (x < trm ? x : trm) + (int)(blockIdx.x >> 3), n_at, n_bt, ai, bi_t);
+  const int64_t i0 = (int64_t)ai * ST::TA, j0 = (int64_t)bi_t * ST::BT;
+  // the tile's rows within their 256-row packed blocks
+  auto operand = [&](const void* p, int64_t r) {
+    const int64_t sub = (r & (kPackRows - 1)) * kRowBytes;
+    return make_rsrc((const unsigned char*)p + (r / kPackRows) * kPackRows * (int64_t)a.K * 2 + sub,
+                     (uint64_t)kPackRows * a.K * 2 - sub);
+  };
+  const rsrc_t ar = operand(a.a, i0), br = operand(a.b, j0);
+  const int nk = a.K / kKS;
+
+#pragma unroll
+  for (int s = 0; s < NBUF; ++s)
+#pragma unroll
+    for (int q = 0; q < L; ++q) small_load<ST>(lds + s * SB, ar, br, wave, lane, (s < nk ? s : nk - 1) * kStep, q);
+  wait_vmem<(NBUF - 1) * L>();  // stage 0 landed
+  __syncthreads();
+
+  f32x4 acc[NA][NB];
+  bf16x8 fa[2][NA], fb[2][NB];
+#pragma unroll
+  for (int bi = 0; bi < NA; ++bi)
+#pragma unroll
+    for (int bj = 0; bj < NB; ++bj) acc[bi][bj] = f32x4{};
+#pragma unroll
+  for (int bj = 0; bj < NB; ++bj)
+    fb[0][bj] = read_operand(lds + ST::TA * kRowBytes, (wt * NB + bj) * 16 + (lane & 15), 0, lane);
+#pragma unroll
+  for (int bi = 0; bi < NA; ++bi) fa[0][bi] = read_operand(lds, (wv * NA + bi) * 16 + (lane & 15), 0, lane);
+
+  int bk = 0;  // buffer of the current stage
+  for (int k = 0; k < nk; ++k) {
+    unsigned char* cb = lds + bk * SB;
+    small_kstep<ST, NA, NB, 0, false>(fa, fb, acc, cb, ar, br, 0, cb, 1, wave, wv, wt, lane);
+    // this wave's reads of stage k and its DMA of stage k + 1 are done; the barrier makes that stage visible and
+    // frees this one's buffer, which takes stage k + NBUF (past the end: the last stage again, never read)
+    wait_lgkm0_vmem<(NBUF - 2) * L>();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (++bk == NBUF) bk = 0;
+    small_kstep<ST, NA, NB, 1, true>(fa, fb, acc, cb, ar, br, (k + NBUF < nk ? k + NBUF : nk - 1) * kStep,
+                                     lds + bk * SB, 0, wave, wv, wt, lane);
+  }
+  wait_vmem<0>();  // no global->LDS request may outlive the workgroup
+
+  // lane l holds B row l % 16 of a block and its A rows 4 (l / 16) .. + 3
+  const int i_lane = (int)i0 + wv * NA * 16 + 4 * (lane >> 4);
+#pragma unroll
+  for (int bj = 0; bj < NB; ++bj) {
+    const int64_t jr = j0 + (wt * NB + bj) * 16 + (lane & 15);
+    if (jr >= a.b_rows) continue;
+#pragma unroll
+    for (int bi = 0; bi < NA; ++bi)
+      if (i_lane + bi * 16 < a.a_rows) *(f32x4*)(a.out + jr * a.ldo + i_lane + bi * 16) = acc[bi][bj];
+  }
 }
 
 }  // namespace

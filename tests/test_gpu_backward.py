@@ -237,6 +237,31 @@ def test_grad_hidden_is_batch_invariant_and_grad_w_micro_batch_invariant():
           "grad_w bitwise across micro-batches 0/128/256/384/640")
 
 
+@pytest.mark.parametrize("T", [1500, 3001, 6999, 12001])
+def test_grad_hidden_output_tiles_agree(T):
+    """grad_hidden takes its output tile by how many tiles fill the chip: at d = 1152 on 256 CUs a pass of 128 rows
+    runs on 64 x 64 tiles, 1500 rows on 64 x 128, 3001 on 128 x 128, 6999 on 128 x 256 and 12001 on 256 x 256 ones
+    (with a half-empty last tile of d and a ragged last row tile). Every row bitwise as in passes of 128, and sampled
+    rows against the oracle within the derived bound; V = 1000 leaves fewer stages than the small tiles' buffers
+    hold at once."""
+    d, V, tau = 1152, 1000, 0.9
+    h, W = inputs(T, d, V, seed=T, w_std=0.05)
+    tok = random_tokens(T, V, T)
+    lp, H, lse = tim.logprobs(h, W, tok, tau, lse=True)
+    gl, ge = _upstream(T, T)
+    run = lambda mb: tim.logprobs_backward(h, W, tok, lse, gl, tau, entropy=H, grad_entropy=ge, micro_batch=mb,
+                                           want_w=False)[0]
+    gh = run(0)
+    assert bits_equal(gh, run(128))
+    rows = np.unique(np.concatenate([[0, 63, 64, 127, 128, T - 1], np.random.default_rng(T).choice(T, 40)]))
+    idx = torch.as_tensor(rows, device="cuda")
+    dacc = oracle.logit_grads(bf16_bits(h.index_select(0, idx)), bf16_bits(W), tok.index_select(0, idx).cpu().numpy(),
+                              tau, gl.index_select(0, idx).cpu().double().numpy(),
+                              ge.index_select(0, idx).cpu().double().numpy())
+    wf = oracle.bf16_to_f64(bf16_bits(W))
+    _bound_check(f"grad_hidden tiles T={T}", gh.index_select(0, idx), dacc @ wf, np.abs(dacc) @ np.abs(wf), 1024)
+
+
 def test_grad_w_accumulation_continues_the_chain():
     """dW(first 256 rows) then += dW(next 444 rows) is bitwise dW(all 700 rows)."""
     T, d, V, tau = 700, 128, 2000, 1.0
