@@ -377,35 +377,65 @@ static hipError_t launch_small(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The output tile of a product and what its rounds over the chip cost: the
+// tiles dealt to the CUs, times one round against a round of 256 x 256 tiles
+// (measured at K = 152064: 3.35 ms; 128 x 256 1.95, 128 x 128 1.25, 64 x 128
+// 0.83, 64 x 64 0.5 ms a round). The smaller the tile the more LDS and cache
+// traffic per flop, so smaller ones only win where larger ones leave CUs idle.
+// grad_hidden at K = 152064: 1001 rows at d = 2048 3.07 ms on 32 tiles of
+// 256 x 256, 0.67 on 256 of 64 x 128; 2000 rows at d = 4096 3.1 ms on 128
+// tiles, 1.95 on 256 of 128 x 256; 3000 rows there stay on 192 tiles of
+// 256 x 256 (2 rounds of 128 x 256 cost more).
+struct GemmShape {
+  int64_t cost;
+  hipError_t (*launch)(const GemmArgs&, hipStream_t);
+};
+static hipError_t launch_whole(const GemmArgs& a, hipStream_t s) {
+  return launch_pass<EpiStore, 2, 4>(gemm_nt_f32<2, 4>, a, a.a_rows, a.b_rows, s);
+}
+static GemmShape best_shape(int64_t a_rows, int64_t b_rows, int64_t cus) {
+  auto cost = [&](int64_t ta, int64_t bt, int64_t round) {
+    return (((a_rows + ta - 1) / ta) * ((b_rows + bt - 1) / bt) + cus - 1) / cus * round;
+  };
+  GemmShape best{cost(256, 256, 100), launch_whole};
+  for (const GemmShape& c : {GemmShape{cost(128, 256, 58), launch_small<2, 4, 4, 4>},
+                             GemmShape{cost(128, 128, 37), launch_small<2, 4, 4, 2>},
+                             GemmShape{cost(64, 128, 24), launch_small<2, 4, 2, 2>},
+                             GemmShape{cost(64, 64, 15), launch_small<2, 2, 2, 2>}})
+    if (c.cost < best.cost) best = c;
+  return best;
+}
+
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.b_rows <= 0 || a.a_rows <= 0) return hipSuccess;
-  if (!a.deep && !a.accumulate) {
-    // The output tile whose rounds over the chip take the least time: the tiles dealt to the CUs, times what one
-    // round of them costs against a round of 256 x 256 tiles (measured at K = 152064: 3.35 ms; 128 x 256 1.95,
-    // 128 x 128 1.25, 64 x 128 0.83, 64 x 64 0.5 ms a round). The smaller the tile the more LDS and cache traffic
-    // per flop, so smaller ones only win where larger ones leave CUs idle. grad_hidden at K = 152064: 1001 rows at
-    // d = 2048 3.07 ms on 32 tiles of 256 x 256, 0.67 on 256 of 64 x 128; 2000 rows at d = 4096 3.1 ms on 128 tiles,
-    // 1.95 on 256 of 128 x 256; 3000 rows there stay on 192 tiles of 256 x 256 (2 rounds of 128 x 256 cost more).
-    const int64_t cus = device_cu_count();
-    auto cost = [&](int64_t ta, int64_t bt, int64_t round) {
-      const int64_t tiles = ((a.a_rows + ta - 1) / ta) * ((a.b_rows + bt - 1) / bt);
-      return cus > 0 ? (tiles + cus - 1) / cus * round : round;
-    };
-    const int64_t c256 = cost(256, 256, 100), c128w = cost(128, 256, 58), c128 = cost(128, 128, 37),
-                  c64w = cost(64, 128, 24), c64 = cost(64, 64, 15);
-    const int64_t best = std::min({c256, c128w, c128, c64w, c64});
-    if (cus > 0 && best < c256) {
-      if (best == c128w) return launch_small<2, 4, 4, 4>(a, s);
-      if (best == c128) return launch_small<2, 4, 4, 2>(a, s);
-      if (best == c64w) return launch_small<2, 4, 2, 2>(a, s);
-      return launch_small<2, 2, 2, 2>(a, s);
+  const int64_t cus = device_cu_count();
+  if (!a.deep && !a.accumulate && cus > 0) {
+    const GemmShape one = best_shape(a.a_rows, a.b_rows, cus);
+    // Or the rows whose 256 x 256 tiles make whole rounds first, then the rest on its own best tile (2 % of a round
+    // for the second launch): 9101 rows at d = 2048 make one round of 8192 rows and 909 rows on 64 x 128 tiles
+    // instead of 2.25 rounds of 128 x 256.
+    const int64_t n_at = (a.a_rows + kVocabTile - 1) / kVocabTile;
+    const int64_t rounds = n_at * (a.b_rows / kPackRows) / cus;
+    const int64_t head = rounds * cus / n_at * kPackRows;  // rows, whole row tiles
+    if (head > 0 && head < a.b_rows) {
+      const GemmShape rest = best_shape(a.a_rows, a.b_rows - head, cus);
+      if (rounds * 100 + rest.cost + 2 < one.cost) {
+        GemmArgs h = a, r = a;
+        h.b_rows = head;
+        r.b = (const __bf16*)a.b + head * a.K;  // packed by 256-row tiles
+        r.b_rows = a.b_rows - head;
+        r.out = a.out + head * a.ldo;
+        const hipError_t e = launch_whole(h, s);
+        return e != hipSuccess ? e : rest.launch(r, s);
+      }
     }
+    return one.launch(a, s);
   }
   if (a.deep) {  // 32-deep stages: a multiple of 4 of them, at least kDeepBufs + 1
     if (a.K % 128 != 0 || a.K / 32 < kDeepBufs + 1) return hipErrorInvalidValue;
     return launch_pass<EpiStore, 2, 4>(gemm_nt_f32_deep<2, 4>, a, a.a_rows, a.b_rows, s);
   }
-  return launch_pass<EpiStore, 2, 4>(gemm_nt_f32<2, 4>, a, a.a_rows, a.b_rows, s);
+  return launch_whole(a, s);
 }
 
 hipError_t launch_transpose(const void* src, bool src_packed, int64_t R, int64_t C, int64_t ld_src, void* dst,

@@ -237,11 +237,12 @@ def test_grad_hidden_is_batch_invariant_and_grad_w_micro_batch_invariant():
           "grad_w bitwise across micro-batches 0/128/256/384/640")
 
 
-@pytest.mark.parametrize("T", [1500, 3001, 6999, 12001])
+@pytest.mark.parametrize("T", [1500, 3001, 6999, 12001, 15001])
 def test_grad_hidden_output_tiles_agree(T):
     """grad_hidden takes its output tile by how many tiles fill the chip: at d = 1152 on 256 CUs a pass of 128 rows
     runs on 64 x 64 tiles, 1500 rows on 64 x 128, 3001 on 128 x 128, 6999 on 128 x 256 and 12001 on 256 x 256 ones
-    (with a half-empty last tile of d and a ragged last row tile). Every row bitwise as in passes of 128, and sampled
+    (15001 as one round of 51 row tiles of those and the other 1945 rows on 128 x 128 tiles;
+    with a half-empty last tile of d and a ragged last row tile). Every row bitwise as in passes of 128, and sampled
     rows against the oracle within the derived bound; V = 1000 leaves fewer stages than the small tiles' buffers
     hold at once."""
     d, V, tau = 1152, 1000, 0.9
