@@ -114,7 +114,7 @@ size_t tim_logprobs_workspace_size(int64_t T, int32_t d, int32_t V, int32_t mode
  * TIM_VOCAB_TILE vocabulary entries, each the merge of its two halves' (lower
  * half first); partials merged by a fixed balanced tree over the tile index.
  * None of this depends on T, mode, micro_batch or a row's position in the
- * batch (a decode batch of at most 128 rows may write the halves' partials
+ * batch (a launch of at most 128 rows may write the halves' partials
  * and merge each pair in the merge pass, which gives the same bits), so with
  * TIM_ORDER_INVARIANT a row's outputs are bitwise identical however it is
  * batched. NaN or Inf in the inputs
@@ -160,7 +160,7 @@ tim_status tim_logprobs_noalloc(const void* hidden, const void* w_vocab, const i
  * tim_logprobs_merge (whose partials are always per whole tile).
  *
  * tim_logprobs_partials: one launch over all T rows (no micro-batching; mode
- * only picks the row tile). Writes T * ceil(V / TIM_VOCAB_TILE) partials of
+ * changes nothing here). Writes T * ceil(V / TIM_VOCAB_TILE) partials of
  * 16 bytes (running max, sum of exponentials, sum of exponential-weighted
  * logit offsets, gathered token logit) into `workspace`, which must hold
  * tim_logprobs_workspace_size(T, d, V, TIM_MODE_ROLLOUT, 0) bytes. Arguments

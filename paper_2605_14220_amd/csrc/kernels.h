@@ -106,8 +106,9 @@ int n_vocab_tiles(int V);
 int n_half_tiles(int V);
 
 // Partials of every (row, vocab tile). rows_per_wg in {64, 128, 256} is the
-// row tile of one workgroup (the split-K4 engine takes 64 or 128); it changes
-// the launch shape only.
+// largest row tile of one workgroup (the split-K4 engine takes 64 or 128),
+// smaller where the smaller tiles all fit the chip at once; it changes the
+// launch shape only.
 hipError_t launch_partials(const LmHeadArgs& a, int rows_per_wg, bool splitk4, hipStream_t s);
 // Partials of every (row, half vocabulary tile), 64 or 128 rows per row tile
 // (by the launch's row count; 2 or 4 waves of 128 x 32): part is

@@ -451,22 +451,34 @@ static hipError_t launch_partials_t(const LmHeadArgs& a, bool persistent, hipStr
   return hipGetLastError();
 }
 
+// The smallest row tile, up to `rows_per_wg`, whose tiles all fit the chip at
+// once (one per CU): such a call is bound by the time of a single tile, so the
+// larger row tile only pays where it saves a round. With a second round the
+// larger one wins (V = 151936, 200 rows: 334 us on 256-row tiles, 433 on
+// 128-row ones), without one the smaller (V = 32000: 45 against 38 us).
+static int fit_row_tile(int64_t rows, int V, int rows_per_wg) {
+  const int64_t n_vt = n_vocab_tiles(V), cus = device_cu_count();
+  for (int rt = 64; rt < rows_per_wg; rt *= 2)
+    if ((rows + rt - 1) / rt * n_vt <= cus) return rt;
+  return rows_per_wg;
+}
+
 hipError_t launch_partials(const LmHeadArgs& a, int rows_per_wg, bool splitk4, hipStream_t s) {
   const bool dump = a.logits != nullptr;
+  const int rt = fit_row_tile(a.rows, a.V, rows_per_wg);
   if (splitk4) {
     // A second accumulator set, so waves of 128 x 32 (64 + 64 accumulators per lane). Eight of them on a 128-row
     // tile put two on each SIMD; it is bound by the LDS operand reads, 10 KB per 16 MFMAs of a wave. Per 2048 rows
     // at d = 4096, V = 151936: 2.55 ms (1.0 PFLOP/s); four waves on a 64-row tile, one per SIMD, 4.13 ms; four of
     // 128 x 64 on a 128-row tile 3.65 ms. The 64-row tile stays for calls of at most 64 rows and where its tiles
-    // all fit the chip at once, where fewer, larger ones would leave CUs idle.
+    // all fit the chip at once.
     if (dump) return launch_partials_t<1, 2, true, true>(a, false, s);
-    const int64_t tiles64 = (a.rows + 63) / 64 * n_vocab_tiles(a.V);
-    return rows_per_wg <= 64 || tiles64 <= device_cu_count() ? launch_partials_t<1, 2, true, false>(a, false, s)
-                                                             : launch_partials_t<1, 4, true, false>(a, true, s);
+    return rt == 64 ? launch_partials_t<1, 2, true, false>(a, false, s) : launch_partials_t<1, 4, true, false>(a, true, s);
   }
-  switch (rows_per_wg) {
+  switch (rt) {
     case 64: return dump ? launch_partials_t<1, 2, false, true>(a, false, s) : launch_partials_t<1, 2, false, false>(a, false, s);
-    case 128: return dump ? launch_partials_t<2, 2, false, true>(a, false, s) : launch_partials_t<2, 2, false, false>(a, false, s);
+    case 128:  // 8 waves of 128 x 32, two per SIMD (four of 128 x 64 were 2-18% slower at 66..128 rows)
+      return dump ? launch_partials_t<1, 4, false, true>(a, true, s) : launch_partials_t<1, 4, false, false>(a, true, s);
     default:  // 256-row tiles, 8 waves; full-size launches persistent
       return dump ? launch_partials_t<2, 4, false, true>(a, true, s) : launch_partials_t<2, 4, false, false>(a, true, s);
   }

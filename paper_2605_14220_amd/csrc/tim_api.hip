@@ -1,10 +1,10 @@
 // C-ABI entry points: argument checks, launch planning, launches.
 //
 // The planner only chooses launch shapes. Rollout mode sends the whole ragged
-// batch in one launch with a row tile sized to the batch (64, 128 or 256 rows
-// per workgroup; a batch of at most 128 rows may take half vocabulary tiles,
-// which run more workgroups per CU);
-// training mode walks the packed stream in micro-batches with 256-row tiles.
+// batch in one launch; training mode walks the packed stream in micro-batches.
+// In both, a launch's row tile follows its rows (64, 128 or 256 rows per
+// workgroup), and a launch of at most 128 rows may take half vocabulary tiles,
+// which run more workgroups per CU.
 // Every shape runs the same per-row instruction sequence.
 
 #include <hip/hip_runtime.h>
@@ -25,11 +25,9 @@ inline float inv_temperature(float temperature) {
 }
 
 // Rows per workgroup for a launch of `rows` rows.
-inline int row_tile_for(int64_t rows, int32_t mode, bool splitk4) {
-  int rt = 256;
-  if (mode == TIM_MODE_ROLLOUT) rt = rows <= 64 ? 64 : (rows <= 128 ? 128 : 256);
-  if (splitk4) rt = rows <= 64 ? 64 : 128;  // the split-K engine keeps a second accumulator set
-  return rt;
+inline int row_tile_for(int64_t rows, bool splitk4) {
+  if (rows <= 64) return 64;
+  return rows <= 128 || splitk4 ? 128 : 256;  // the split-K engine keeps a second accumulator set
 }
 
 // Device scratch of tim_logprobs_noalloc (one copy per GPU, for the life of
@@ -60,8 +58,6 @@ tim_status run_logprobs(const void* hidden, const void* w_vocab, const int32_t* 
   tim_status st = TIM_OK;
   const bool splitk4 = order == TIM_ORDER_SPLITK4;
   const int64_t step = tim::rows_per_launch(T, d, mode, micro_batch);
-  const int tb = row_tile_for(step, mode, splitk4);
-  const bool halves = !splitk4 && tim::uses_half_tiles(step, mode) && tim::prefer_half_tiles(V, step);
   const float inv_tau = inv_temperature(temperature);
   const __bf16* h = (const __bf16*)hidden;
   tim::Partial* part = (tim::Partial*)workspace;
@@ -80,12 +76,17 @@ tim_status run_logprobs(const void* hidden, const void* w_vocab, const int32_t* 
     a.logits = nullptr;
     float* ent = entropy ? entropy + t0 : nullptr;
     float* ls = lse ? lse + t0 : nullptr;
+    // a launch of few rows takes half vocabulary tiles where the workspace (sized for whole launches) holds them
+    const bool halves = !splitk4 && rows <= tim::kHalfTileRows &&
+                        (size_t)rows * tim::n_half_tiles_of(V) * 16u <=
+                            tim::workspace_bytes(T, d, V, mode, micro_batch) &&
+                        tim::prefer_half_tiles(V, rows);
     if (halves) {
       st = hip_status(tim::launch_partials_halves(a, stream));
       if (st != TIM_OK) return st;
       st = hip_status(tim::launch_merge_halves(part, tokens + t0, rows, V, logp + t0, ent, ls, stream));
     } else {
-      st = hip_status(tim::launch_partials(a, tb, splitk4, stream));
+      st = hip_status(tim::launch_partials(a, row_tile_for(rows, splitk4), splitk4, stream));
       if (st != TIM_OK) return st;
       st = hip_status(tim::launch_merge(part, tokens + t0, rows, V, splitk4, logp + t0, ent, ls, stream));
     }
@@ -151,7 +152,7 @@ tim_status tim_logprobs_partials(const void* hidden, const void* w_vocab, const 
   a.inv_tau = inv_temperature(temperature);
   a.part = (tim::Partial*)workspace;
   a.logits = nullptr;
-  return hip_status(tim::launch_partials(a, row_tile_for(T, mode, splitk4), splitk4, stream));
+  return hip_status(tim::launch_partials(a, row_tile_for(T, splitk4), splitk4, stream));
 }
 
 tim_status tim_logprobs_merge(const void* workspace, const int32_t* tokens, int64_t T, int32_t V,

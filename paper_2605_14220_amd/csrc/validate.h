@@ -51,8 +51,9 @@ inline int64_t rows_per_launch(int64_t T, int32_t d, int32_t mode, int64_t micro
   return rows > cap ? cap : rows;
 }
 
-// Rollout launches of at most this many rows (decode batches) may form their
-// partials over half vocabulary tiles; their workspace covers that case.
+// Launches of at most this many rows may form their partials over half
+// vocabulary tiles where the workspace holds them. Rollout calls of such
+// launches (decode batches) have a workspace that always does.
 constexpr int64_t kHalfTileRows = 128;
 inline bool uses_half_tiles(int64_t rows, int32_t mode) { return mode == TIM_MODE_ROLLOUT && rows <= kHalfTileRows; }
 

@@ -280,3 +280,29 @@ def test_decode_repeated_calls_identical():
             for _ in range(4):
                 dec, _ = _decode(h, W, tok, 0.7)
                 _same(dec, trn)
+
+
+@pytest.mark.parametrize("V,cuts", [
+    # 274 tiles: no smaller tile fits one round, so 64- and 128-row tiles serve calls of at most that many rows
+    (274 * 256 - 5, [(0, 64), (3, 68), (64, 192), (100, 229)]),
+    # 32 tiles on 256 CUs: 64-row tiles up to 512 rows, 128-row ones up to 1024
+    (32 * 256 - 100, [(0, 1), (0, 64), (7, 72), (0, 512), (11, 524), (0, 1024), (100, 1130)]),
+])
+def test_row_tiles_bitwise_equal(V, cuts):
+    """The row tile of a launch follows its rows and vocabulary (in both modes, and for the last micro-batch of a
+    stream); row subsets that take 64- and 128-row tiles give bitwise the rows of one launch on 256-row ones."""
+    T, d, tau = 2300, 256, 0.9
+    print(f"case row tiles V={V}", flush=True)
+    h, W = inputs(T, d, V, seed=V % 997)
+    tok = _tokens(T, V, seed=5)
+    ref = tim.logprobs(h, W, tok, tau, lse=True)
+    for a, b in cuts:
+        for mode in (Mode.TRAINING, Mode.ROLLOUT):
+            got = tim.logprobs(h[a:b].contiguous(), W, tok[a:b].contiguous(), tau, mode=mode, lse=True)
+            _same(got, [x[a:b].contiguous() for x in ref])
+    # micro-batches whose last one is short: of 50 rows (half tiles within the stream's workspace) and of 100
+    _same(tim.logprobs(h, W, tok, tau, lse=True, micro_batch=250), ref)
+    _same(tim.logprobs(h, W, tok, tau, lse=True, micro_batch=1100), ref)
+    lp, H = oracle_rows(h, W, tok, tau, rows=range(0, T, 23))
+    check_close("row tiles logp", ref[0], lp, TOL_LOGP, rows=range(0, T, 23))
+    check_close("row tiles entropy", ref[1], H, TOL_ENT, rows=range(0, T, 23))
