@@ -16,12 +16,11 @@
 //   dg_k = sum_t G_tk x_tk r_t   as fixed-order column sums over blocks of
 //          rows, then over the blocks in order (no atomics). Blocks are 256
 //          rows whose rows go in order, except in calls of at least 65536 rows
-//          of width 2048 or 4096, whose grad_x pass also forms the block sums:
-//          there a block is 4 rpw rows, rpw = max(64, ceil(T / (4 R))) with
-//          R = 1024 at d = 2048 and 512 at d = 4096 (the blocks a 256-CU chip
-//          holds at once), each quarter of rpw rows goes in order and the
-//          quarters combine as (q0 + q1) + (q2 + q3). The order so depends on
-//          (T, d) only.
+//          of width 2048 or 4096: there a block is 4 rpw rows, rpw = max(64,
+//          ceil(T / (4 R))) with R = 1024 at d = 2048 and 512 at d = 4096 (the
+//          blocks a 256-CU chip holds at once), each quarter of rpw rows goes
+//          in order and the quarters combine as (q0 + q1) + (q2 + q3). The
+//          order so depends on (T, d) only.
 // Each is one HBM pass over the rows; the norm costs ~0.2% of the LM head it
 // feeds, so it runs as its own launch ahead of the head instead of inside the
 // head's MFMA loop, which would repeat it once per vocabulary tile and add
@@ -29,6 +28,7 @@
 
 #include <hip/hip_runtime.h>
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -147,15 +147,12 @@ __device__ __forceinline__ void out_chunk_dx(float4* __restrict__ out, int c, ui
   out[2 * c + 1] = float4{o[4], o[5], o[6], o[7]};
 }
 
-// Same two-mode structure as the forward (NCL > 0: the row's x, G and gamma
-// chunks kept in registers between the passes).
+// One row's dx by one wave. Same two-mode structure as the forward (NCL > 0:
+// the row's x, G and gamma chunks kept in registers between the passes).
 template <int NCL>
-__global__ __launch_bounds__(256) void rmsnorm_bwd_x(const uint4* __restrict__ x, const uint4* __restrict__ gamma,
-                                                     const float* __restrict__ rstd, const float4* __restrict__ G,
-                                                     int64_t T, int d, float4* __restrict__ dx) {
-  const int lane = threadIdx.x & 63;
-  const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t >= T) return;
+__device__ __forceinline__ void row_dx(const uint4* __restrict__ x, const uint4* __restrict__ gamma,
+                                       const float* __restrict__ rstd, const float4* __restrict__ G, int64_t t, int d,
+                                       float4* __restrict__ dx, int lane) {
   const int nc = NCL > 0 ? NCL * 64 : d / 8;
   const uint4* xr = x + t * nc;
   const float4* gr = G + t * (int64_t)(d / 4);
@@ -187,6 +184,14 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_x(const uint4* __restrict__ x
     for (int c = lane; c < nc; c += 64)
       out_chunk_dx(out, c, xr[c], gr[2 * c], gr[2 * c + 1], gamma_chunk(gamma, c), r, c2);
   }
+}
+
+template <int NCL>
+__global__ __launch_bounds__(256) void rmsnorm_bwd_x(const uint4* __restrict__ x, const uint4* __restrict__ gamma,
+                                                     const float* __restrict__ rstd, const float4* __restrict__ G,
+                                                     int64_t T, int d, float4* __restrict__ dx) {
+  const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (t < T) row_dx<NCL>(x, gamma, rstd, G, t, d, dx, threadIdx.x & 63);
 }
 
 // Widths whose rows stay in registers: grad_x and the block's grad_gamma
@@ -261,34 +266,91 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_fused(const uint4* __restrict
   }
 }
 
-// Column sums of G x r over one block of up to 256 rows, rows in order.
-__global__ __launch_bounds__(256) void rmsnorm_dgamma_part(const uint16_t* __restrict__ x,
-                                                           const float* __restrict__ rstd,
-                                                           const float* __restrict__ G, int64_t T, int d,
-                                                           float* __restrict__ part) {
-  const int k = blockIdx.x * 256 + threadIdx.x;
-  if (k >= d) return;
-  const int64_t t0 = (int64_t)blockIdx.y * 256;
-  const int64_t t1 = (T - t0) < 256 ? T : t0 + 256;
-  float acc = 0.f;
-  int64_t t = t0;
-  // 8 rows' loads issued ahead of their terms (the adds stay in row order)
-  for (; t + 8 <= t1; t += 8) {
-    float xv[8], gv[8], rv[8];
+// Column sums of G x r over block `blk` of up to 256 rows, two columns per
+// thread; cb the workgroup's range of 512 columns. The rows go in order, or
+// with `quarters` each 64-row quarter does, as (q0 + q1) + (q2 + q3).
+__device__ __forceinline__ void dgamma_block(const uint32_t* __restrict__ x, const float* __restrict__ rstd,
+                                             const float2* __restrict__ G, int64_t T, int d, int quarters, int64_t blk,
+                                             int cb, float2* __restrict__ part) {
+  const int k = cb * 256 + threadIdx.x, d2 = d / 2;  // column pair
+  if (k >= d2) return;
+  int64_t t = blk * 256;
+  const int64_t t1 = (T - t) < 256 ? T : t + 256;
+  const int chain = quarters ? 64 : 256;
+  float2 even = float2{0.f, 0.f}, total = float2{0.f, 0.f};
+#pragma unroll 1
+  for (int q = 0; q * chain < 256; ++q) {
+    const int64_t te = (t1 - t) < chain ? t1 : t + chain;
+    float2 acc = float2{0.f, 0.f};
+    auto add = [&](uint32_t xv, float2 gv, float rv) {
+      acc.x = acc.x + (gv.x * bf16_lo(xv)) * rv;
+      acc.y = acc.y + (gv.y * bf16_hi(xv)) * rv;
+    };
+    // 16 rows' loads issued ahead of their terms (the adds stay in row order)
+    for (; t + 16 <= te; t += 16) {
+      uint32_t xv[16];
+      float2 gv[16];
+      float rv[16];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      xv[i] = __uint_as_float((uint32_t)x[(t + i) * d + k] << 16);
-      gv[i] = G[(t + i) * d + k];
-      rv[i] = rstd[t + i];
+      for (int i = 0; i < 16; ++i) {
+        xv[i] = x[(t + i) * d2 + k];
+        gv[i] = G[(t + i) * d2 + k];
+        rv[i] = rstd[t + i];
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) add(xv[i], gv[i], rv[i]);
     }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc = acc + (gv[i] * xv[i]) * rv[i];
+    for (; t < te; ++t) add(x[t * d2 + k], G[t * d2 + k], rstd[t]);
+    if (!quarters) total = acc;
+    else if ((q & 1) == 0) even = acc;
+    else if (q == 1) total = float2{even.x + acc.x, even.y + acc.y};
+    else total = float2{total.x + (even.x + acc.x), total.y + (even.y + acc.y)};
   }
-  for (; t < t1; ++t) {
-    const float xv = __uint_as_float((uint32_t)x[t * d + k] << 16);
-    acc = acc + (G[t * d + k] * xv) * rstd[t];
+  part[blk * d2 + k] = total;
+}
+
+__global__ __launch_bounds__(256) void rmsnorm_dgamma_part(const uint32_t* __restrict__ x,
+                                                           const float* __restrict__ rstd,
+                                                           const float2* __restrict__ G, int64_t T, int d,
+                                                           int quarters, float2* __restrict__ part) {
+  dgamma_block(x, rstd, G, T, d, quarters, blockIdx.y, blockIdx.x, part);
+}
+
+// grad_x and grad_gamma's block sums in one launch: workgroups of 4 rows of dx
+// and workgroups of one block's column sums, ordered so that the two run over
+// the same rows at about the same time and x and G come from HBM once, the
+// second read from the memory-side cache. The column sums' workgroups (256 rows
+// in order each, so long ones) go kLead blocks ahead, to end with the others (8
+// and 16 blocks alike; 4 1% and none 2-8% slower). Bound by the cache misses of
+// the XCDs, both reads and the writes (6.8 TB/s): 16384 rows at d = 4096
+// 200 -> 164 us against two launches, of which 114 would be one pass over HBM.
+constexpr int kLead = 8;
+template <int NCL>
+__global__ __launch_bounds__(256) void rmsnorm_bwd_both(const uint4* __restrict__ x, const uint4* __restrict__ gamma,
+                                                        const float* __restrict__ rstd, const float4* __restrict__ G,
+                                                        int64_t T, int d, int n_cb, int quarters, float4* __restrict__ dx,
+                                                        float* __restrict__ part) {
+  const int64_t n_blocks = (T + 255) / 256;
+  const int64_t ahead = (n_blocks < kLead ? n_blocks : kLead) * n_cb;
+  int64_t blk = -1;
+  int cb = 0;
+  if (blockIdx.x < ahead) {
+    blk = blockIdx.x / n_cb;
+    cb = blockIdx.x % n_cb;
+  } else {
+    const int64_t r = blockIdx.x - ahead;
+    const int64_t g = r / (64 + n_cb);
+    const int in = (int)(r % (64 + n_cb));
+    if (in < 64) {
+      const int64_t t = g * 256 + in * 4 + (threadIdx.x >> 6);
+      if (t < T) row_dx<NCL>(x, gamma, rstd, G, t, d, dx, threadIdx.x & 63);
+      return;
+    }
+    blk = g + kLead;
+    cb = in - 64;
+    if (blk >= n_blocks) return;
   }
-  part[(int64_t)blockIdx.y * d + k] = acc;
+  dgamma_block((const uint32_t*)x, rstd, (const float2*)G, T, d, quarters, blk, cb, (float2*)part);
 }
 
 // dg_k (+)= the blocks' sums in block order.
@@ -312,26 +374,31 @@ __global__ __launch_bounds__(256) void rmsnorm_dgamma_final(const float* __restr
 
 }  // namespace
 
+// f(NCL) with NCL = d / 512 as a compile-time constant where a lane keeps its
+// chunks of the row in registers (d a multiple of 512 up to 512 MAXN), else f(0).
+template <int MAXN, int N = MAXN, class F>
+static void with_chunks(int d, F f) {
+  if constexpr (N == 0) f(std::integral_constant<int, 0>{});
+  else if (d == 512 * N) f(std::integral_constant<int, N>{});
+  else with_chunks<MAXN, N - 1>(d, f);
+}
+constexpr int kFwdChunks = 16, kBwdChunks = 10;  // as many as the registers hold
+static bool keeps_row(int d) { return d % 512 == 0 && d <= 512 * kBwdChunks; }
+
 hipError_t launch_rmsnorm(const void* x, const void* gamma, int64_t T, int d, float eps, void* h, float* rstd,
                           hipStream_t s) {
   if (T <= 0) return hipSuccess;
   const int64_t nb = (T + 3) / 4;
   if (nb > 0x7fffffff) return hipErrorInvalidValue;
-  const dim3 g((unsigned)nb), b(256);
-  const uint4* xp = (const uint4*)x;
-  const uint4* gp = (const uint4*)gamma;
-  switch (d) {  // widths whose rows stay in registers
-    case 2048: hipLaunchKernelGGL(rmsnorm_fwd<4>, g, b, 0, s, xp, gp, T, d, eps, (uint4*)h, rstd); break;
-    case 4096: hipLaunchKernelGGL(rmsnorm_fwd<8>, g, b, 0, s, xp, gp, T, d, eps, (uint4*)h, rstd); break;
-    case 5120: hipLaunchKernelGGL(rmsnorm_fwd<10>, g, b, 0, s, xp, gp, T, d, eps, (uint4*)h, rstd); break;
-    case 8192: hipLaunchKernelGGL(rmsnorm_fwd<16>, g, b, 0, s, xp, gp, T, d, eps, (uint4*)h, rstd); break;
-    default: hipLaunchKernelGGL(rmsnorm_fwd<0>, g, b, 0, s, xp, gp, T, d, eps, (uint4*)h, rstd); break;
-  }
+  with_chunks<kFwdChunks>(d, [&](auto n) {
+    hipLaunchKernelGGL(rmsnorm_fwd<n.value>, dim3((unsigned)nb), dim3(256), 0, s, (const uint4*)x, (const uint4*)gamma,
+                       T, d, eps, (uint4*)h, rstd);
+  });
   return hipGetLastError();
 }
 
-// Rows from which the norm backward takes grad_gamma in the grad_x pass.
-constexpr int64_t kFusedNormRows = 65536;
+// Rows from which the norm backward sums grad_gamma's blocks by quarters.
+constexpr int64_t kQuarterRows = 65536;
 
 template <int NCL>
 static hipError_t launch_fused(const void* x, const void* gamma, const float* rstd, const float* grad_h, int64_t T,
@@ -349,49 +416,62 @@ static hipError_t launch_fused(const void* x, const void* gamma, const float* rs
 hipError_t launch_rmsnorm_backward(const void* x, const void* gamma, const float* rstd, const float* grad_h,
                                    int64_t T, int d, float* grad_x, float* grad_gamma, int accumulate, float* part,
                                    hipStream_t s) {
-  // Large calls at the widths whose rows stay in registers take grad_gamma's
-  // block sums in the grad_x pass (with or without grad_x): one workgroup per
-  // block of rows walks its rows in order, which pays once there are enough
-  // blocks to fill the chip. The choice depends on (T, d) only.
-  const bool fused = grad_gamma && (d == 2048 || d == 4096) && T >= kFusedNormRows;
-  // Rows per wave: 64, or more where that many blocks would not all be
-  // resident at once on a 256-CU MI355X (two workgroups per CU at d = 4096,
-  // four at 2048), which would leave a second round of a few blocks walking
-  // their rows alone. A constant, so the order depends on (T, d) only.
+  // From kQuarterRows rows at d = 2048 and 4096 the blocks' sums go by quarters.
+  // With at least 256 rows per resident workgroup (two per CU of a 256-CU
+  // MI355X at d = 4096, four at 2048) they are taken in the grad_x pass, with
+  // or without grad_x: one workgroup per block walks its rows in order and
+  // reads x and G once (138000 rows at d = 4096 with the forward: 1.54 ms, 1.64
+  // as rmsnorm_bwd_both). With fewer rows those blocks leave CUs idle (66000
+  // rows: 0.95 against 0.79 ms). The choice, and so grad_gamma's order, depends
+  // on (T, d) only.
   const int64_t resident = d == 2048 ? 1024 : 512;
-  const int rpw = (int)std::max<int64_t>(64, (T + 4 * resident - 1) / (4 * resident));
+  const int quarters = (d == 2048 || d == 4096) && T >= kQuarterRows;
+  const bool fused = grad_gamma && quarters && T >= 256 * resident;
+  // Rows per wave: all the blocks resident at once, none left for a second
+  // round of a few blocks walking their rows alone.
+  const int rpw = (int)((T + 4 * resident - 1) / (4 * resident));
   if (fused && T > 0) {
     if ((T + 255) / 256 > 65535) return hipErrorInvalidValue;
     const hipError_t e = d == 2048 ? launch_fused<4>(x, gamma, rstd, grad_h, T, rpw, grad_x, part, s)
                                    : launch_fused<8>(x, gamma, rstd, grad_h, T, rpw, grad_x, part, s);
     if (e != hipSuccess) return e;
   }
-  if (T > 0 && grad_x && !fused) {
-    const int64_t nb = (T + 3) / 4;
-    if (nb > 0x7fffffff) return hipErrorInvalidValue;
-    const dim3 g((unsigned)nb), b(256);
+  const int64_t n_blocks = fused ? (T + 4 * rpw - 1) / (4 * rpw) : (T + 255) / 256;
+  const unsigned n_cb = (unsigned)((d + 511) / 512);  // workgroups of 512 columns
+  if (grad_gamma && n_blocks > 65535) return hipErrorInvalidValue;
+  if (T > 0 && !fused && (grad_x || grad_gamma)) {
+    const dim3 b(256);
     const uint4* xp = (const uint4*)x;
     const uint4* gp = (const uint4*)gamma;
     const float4* Gp = (const float4*)grad_h;
-    switch (d) {  // widths whose rows stay in registers
-      case 2048: hipLaunchKernelGGL(rmsnorm_bwd_x<4>, g, b, 0, s, xp, gp, rstd, Gp, T, d, (float4*)grad_x); break;
-      case 4096: hipLaunchKernelGGL(rmsnorm_bwd_x<8>, g, b, 0, s, xp, gp, rstd, Gp, T, d, (float4*)grad_x); break;
-      case 5120: hipLaunchKernelGGL(rmsnorm_bwd_x<10>, g, b, 0, s, xp, gp, rstd, Gp, T, d, (float4*)grad_x); break;
-      default: hipLaunchKernelGGL(rmsnorm_bwd_x<0>, g, b, 0, s, xp, gp, rstd, Gp, T, d, (float4*)grad_x); break;
+    float4* dxp = (float4*)grad_x;
+    // one launch for both where the rows stay in registers (a row read twice by the grad_x pass would be read a
+    // third time from the cache: 3000 rows at d = 8192 106 us in two launches, 110 in one)
+    const bool both = grad_x && grad_gamma && keeps_row(d);
+    if (both) {
+      const int64_t nb = n_blocks * (64 + n_cb) + std::min<int64_t>(n_blocks, kLead) * n_cb;
+      if (nb > 0x7fffffff) return hipErrorInvalidValue;
+      with_chunks<kBwdChunks>(d, [&](auto n) {
+        hipLaunchKernelGGL(rmsnorm_bwd_both<n.value>, dim3((unsigned)nb), b, 0, s, xp, gp, rstd, Gp, T, d, (int)n_cb,
+                           quarters, dxp, part);
+      });
+    } else {
+      if (grad_x) {
+        const int64_t nb = (T + 3) / 4;
+        if (nb > 0x7fffffff) return hipErrorInvalidValue;
+        with_chunks<kBwdChunks>(d, [&](auto n) {
+          hipLaunchKernelGGL(rmsnorm_bwd_x<n.value>, dim3((unsigned)nb), b, 0, s, xp, gp, rstd, Gp, T, d, dxp);
+        });
+      }
+      if (grad_gamma)
+        hipLaunchKernelGGL(rmsnorm_dgamma_part, dim3(n_cb, (unsigned)n_blocks), b, 0, s, (const uint32_t*)x, rstd,
+                           (const float2*)grad_h, T, d, quarters, (float2*)part);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   if (grad_gamma) {
-    const int64_t n_blocks = fused ? (T + 4 * rpw - 1) / (4 * rpw) : (T + 255) / 256;
-    if (n_blocks > 65535) return hipErrorInvalidValue;
     const unsigned gx = (unsigned)((d + 255) / 256);
-    if (n_blocks > 0 && !fused) {
-      hipLaunchKernelGGL(rmsnorm_dgamma_part, dim3(gx, (unsigned)n_blocks), dim3(256), 0, s, (const uint16_t*)x, rstd,
-                         grad_h, T, d, part);
-      const hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-    }
     hipLaunchKernelGGL(rmsnorm_dgamma_final, dim3(gx), dim3(256), 0, s, part, (int)n_blocks, d, accumulate,
                        grad_gamma);
     return hipGetLastError();

@@ -154,6 +154,28 @@ def test_rmsnorm_backward_vs_oracle(T, d, with_gamma):
     assert torch.allclose(buf, 2 * gg, rtol=1e-6, atol=0)
 
 
+@pytest.mark.parametrize("T,d", [(1, 512), (255, 1536), (257, 2048), (2049, 512), (2305 + 17, 3584), (300, 5120)])
+def test_rmsnorm_backward_one_launch_equals_two(T, d):
+    """Widths whose rows stay in registers take grad_x and grad_gamma's block sums in one launch (blocks of 256 rows,
+    the column sums up to 8 blocks ahead of the rows): the bits of the two alone, at one block, at its edges, with
+    more blocks than the lead and a last one of 17 rows, and grad_gamma against the oracle within its bound."""
+    print(f"case one launch T={T} d={d}", flush=True)
+    x = _x(T, d, T + d)
+    g = _gamma(d, d + 1)
+    _, rstd = tim.rmsnorm(x, g, 1e-6)
+    G = torch.randn(T, d, generator=torch.Generator(device="cpu").manual_seed(T)).cuda()
+    gx, gg = tim.rmsnorm_backward(x, g, rstd, G)
+    gx1, _ = tim.rmsnorm_backward(x, g, rstd, G, want_gamma=False)
+    _, gg1 = tim.rmsnorm_backward(x, g, rstd, G, want_x=False)
+    assert bits_equal(gx, gx1) and bits_equal(gg, gg1)
+    Gn = G.double().cpu().numpy()
+    _, dg = oracle.rmsnorm_grads(bf16_bits(x), bf16_bits(g), 1e-6, Gn)
+    xf = oracle.bf16_to_f64(bf16_bits(x))
+    r = 1.0 / np.sqrt((xf * xf).mean(axis=1) + 1e-6)
+    bound = (256 + T / 256 + 32) * U * np.abs(Gn * xf * r[:, None]).sum(axis=0) + 1e-30
+    assert (np.abs(gg.double().cpu().numpy() - dg) <= bound).all()
+
+
 def test_rmsnorm_degenerate_calls():
     d = 64
     buf = torch.full((d,), 5.0, device="cuda")
@@ -173,9 +195,9 @@ def test_rmsnorm_degenerate_calls():
                                             (4096, True, 131072 + 77), (2048, False, 262144 + 77)])
 def test_rmsnorm_backward_large_call_vs_oracle(d, with_gamma, T):
     """Calls of at least 65536 rows at d = 2048 / 4096 form grad_gamma's block
-    sums in the grad_x pass (each wave's rows in order, then (q0 + q1) + (q2 +
-    q3) per block; above 131072 rows at d = 4096, 262144 at d = 2048, a wave
-    takes more than 64 rows): grad_gamma against the oracle within its bound, grad_x bitwise equal
+    sums by quarters (each quarter's rows in order, then (q0 + q1) + (q2 + q3)
+    per block; above 131072 rows at d = 4096, 262144 at d = 2048, the grad_x
+    pass's own waves form them and take more than 64 rows): grad_gamma against the oracle within its bound, grad_x bitwise equal
     to the same rows evaluated alone (the smaller call's path) and to the
     oracle on sampled rows, and grad_gamma without grad_x the same bits."""
     print(f"case large T={T} d={d} gamma={with_gamma}", flush=True)
