@@ -4,10 +4,8 @@
 // response and averaged over the responses, with its gradient with respect to
 // the current log-probs and the zero-centred contribution C(r) = -(r - 1) A.
 //
-// One workgroup of 256 threads per response, as the sequence-level
-// statistics: thread i takes the tokens i, i + 256, ... of the response in
-// order, in fp64; the response's sum combines the 256 partial sums with a
-// fixed tree. delta = logp - logp_old is exact in fp64, and the clip decision
+// One workgroup per response, as the sequence-level statistics: the token terms
+// in fp64, summed in response_sum's order. delta = logp - logp_old is exact in fp64, and the clip decision
 // is taken on it exactly: with A > 0 the clipped term is the minimum iff
 // r = e^delta > 1 + eps_high, i.e. delta > log1p(eps_high); with A < 0 iff
 // delta < log1p(-eps_low); the thresholds are formed once in fp64 on the host.
@@ -19,18 +17,8 @@
 namespace tim {
 namespace {
 
-constexpr int kPpoThreads = 256;
-
-__device__ __forceinline__ double block_sum(double acc, double* wsum) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) wsum[wave] = acc;
-  __syncthreads();
-  return (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
-}
-
-__global__ __launch_bounds__(kPpoThreads) void ppo_kernel(const float* __restrict__ lp, const float* __restrict__ lo,
+template <int G>
+__global__ __launch_bounds__(G * kChains) void ppo_kernel(const float* __restrict__ lp, const float* __restrict__ lo,
                                                           const float* __restrict__ adv, const float* __restrict__ wt,
                                                           int64_t T, const int64_t* __restrict__ cu, PpoParams p,
                                                           double* seq_loss, float* token_loss, float* grad,
@@ -39,8 +27,7 @@ __global__ __launch_bounds__(kPpoThreads) void ppo_kernel(const float* __restric
   int64_t s0 = cu[j], s1 = cu[j + 1];
   s0 = s0 < 0 ? 0 : (s0 > T ? T : s0);
   s1 = s1 < s0 ? s0 : (s1 > T ? T : s1);
-  double acc = 0.0;
-  for (int64_t t = s0 + threadIdx.x; t < s1; t += kPpoThreads) {
+  const double S = response_sum<G>(s0, s1, [&](int64_t t) {
     const double delta = (double)lp[t] - (double)lo[t];
     const double a = (double)adv[t];
     const double w = wt ? (double)wt[t] : 1.0;
@@ -52,21 +39,15 @@ __global__ __launch_bounds__(kPpoThreads) void ppo_kernel(const float* __restric
     if (grad) grad[t] = clip ? 0.f : (float)(w * (-a * r) * p.inv_n);
     if (contrib) contrib[t] = (float)(-(r - 1.0) * a);
     if (clipped) clipped[t] = clip ? 1 : 0;
-    acc += tl;
-  }
-  __shared__ double wsum[kPpoThreads / 64];
-  const double S = block_sum(acc, wsum);
+    return tl;
+  });
   if (threadIdx.x == 0 && seq_loss) seq_loss[j] = S;
 }
 
-// The batch loss: the response sums in a fixed order (thread i takes
-// responses i, i + 256, ...), then the same tree, divided by n.
-__global__ __launch_bounds__(kPpoThreads) void ppo_batch_kernel(const double* __restrict__ seq_loss, int64_t n,
-                                                                double* batch_loss) {
-  double acc = 0.0;
-  for (int64_t j = threadIdx.x; j < n; j += kPpoThreads) acc += seq_loss[j];
-  __shared__ double wsum[kPpoThreads / 64];
-  const double S = block_sum(acc, wsum);
+// The batch loss: the response sums in the same order as a response's tokens, divided by n.
+__global__ __launch_bounds__(kChains) void ppo_batch_kernel(const double* __restrict__ seq_loss, int64_t n,
+                                                            double* batch_loss) {
+  const double S = response_sum<1>(0, n, [&](int64_t j) { return seq_loss[j]; });
   if (threadIdx.x == 0) batch_loss[0] = S / (double)n;
 }
 
@@ -78,11 +59,16 @@ hipError_t launch_ppo_loss(const float* logp, const float* logp_old, const float
                            hipStream_t s) {
   if (n_seq <= 0) return hipSuccess;
   if (n_seq > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(ppo_kernel, dim3((unsigned)n_seq), dim3(kPpoThreads), 0, s, logp, logp_old, advantages, weight,
-                     T, cu_seqlens, p, seq_loss, token_loss, grad, contrib, clipped);
+  const dim3 g((unsigned)n_seq);
+  if (response_blocks(T, n_seq) > 1)
+    hipLaunchKernelGGL(ppo_kernel<4>, g, dim3(4 * kChains), 0, s, logp, logp_old, advantages, weight, T, cu_seqlens, p,
+                       seq_loss, token_loss, grad, contrib, clipped);
+  else
+    hipLaunchKernelGGL(ppo_kernel<1>, g, dim3(kChains), 0, s, logp, logp_old, advantages, weight, T, cu_seqlens, p,
+                       seq_loss, token_loss, grad, contrib, clipped);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !batch_loss) return e;
-  hipLaunchKernelGGL(ppo_batch_kernel, dim3(1), dim3(kPpoThreads), 0, s, (const double*)seq_loss, n_seq, batch_loss);
+  hipLaunchKernelGGL(ppo_batch_kernel, dim3(1), dim3(kChains), 0, s, (const double*)seq_loss, n_seq, batch_loss);
   return hipGetLastError();
 }
 
