@@ -131,7 +131,8 @@ def _ptr(t):
 
 
 def _stream(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    # the handle alone: building the Stream object of torch.cuda.current_stream takes 2 us of every call
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def _require_gpu(*tensors):
@@ -450,12 +451,16 @@ def ppo_loss(logp: torch.Tensor, logp_old: torch.Tensor, advantages: torch.Tenso
     dev = logp.device
     if out is not None:
         _require_gpu(*out.values())
-    out = out or {"seq_loss": torch.zeros(n, dtype=torch.float64, device=dev),
-           "batch_loss": torch.zeros(1, dtype=torch.float64, device=dev),
-           "token_loss": torch.zeros(T, dtype=torch.float32, device=dev),
-           "grad": torch.zeros(T, dtype=torch.float32, device=dev),
-           "contribution": torch.zeros(T, dtype=torch.float32, device=dev),
-           "clipped": torch.zeros(T, dtype=torch.uint8, device=dev)}
+    if not out:
+        # every response's sum and the batch loss are written (with no response nothing is); only the tokens outside
+        # the responses need clearing
+        sums = torch.empty if n > 0 else torch.zeros
+        tl, gr, ct = (torch.empty(T, dtype=torch.float32, device=dev) for _ in range(3))
+        torch._foreach_zero_([tl, gr, ct])  # one launch
+        out = {"seq_loss": sums(n, dtype=torch.float64, device=dev),
+               "batch_loss": sums(1, dtype=torch.float64, device=dev),
+               "token_loss": tl, "grad": gr, "contribution": ct,
+               "clipped": torch.zeros(T, dtype=torch.uint8, device=dev)}
     _check(lib.tim_ppo_loss(_ptr(logp), _ptr(logp_old), _ptr(advantages), _ptr(weight), T, _ptr(cu_seqlens), n,
                             float(eps_low), float(eps_high), _ptr(out["seq_loss"]), _ptr(out["batch_loss"]),
                             _ptr(out["token_loss"]), _ptr(out["grad"]), _ptr(out["contribution"]),

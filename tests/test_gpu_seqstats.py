@@ -131,3 +131,25 @@ def test_no_responses_is_noop():
     cu = torch.zeros(1, dtype=torch.int64, device="cuda")
     s, k, w = tim.mismatch_seq(a, a, cu)
     assert s.numel() == 0 and k.numel() == 0 and (w == 0).all()
+
+
+@pytest.mark.parametrize("L", [513, 767, 1023, 1024, 1025, 2049, 5000])
+def test_blocks_of_threads_agree(L):
+    """A response alone in its stream (more than 512 tokens a response: four blocks of threads, terms through LDS)
+    and the same one followed by empty responses (one block): the score, the weights and every PPO output bit for
+    bit, kept and rejected, with lengths on and around the 1024 tokens four blocks take at a time."""
+    a, b, cu = _stream(L, [L])
+    ag, bg = torch.as_tensor(a).cuda(), torch.as_tensor(b).cuda()
+    adv = torch.as_tensor(np.random.default_rng(L).standard_normal(L).astype(np.float32)).cuda()
+    c1 = torch.as_tensor(cu).cuda()
+    cn = torch.cat([c1, c1[-1:].expand(L)])  # L + 1 responses, T / n < 1
+    for tau in (0.0, 1e9):
+        one = tim.mismatch_seq(ag, bg, c1, tau_seq=tau)
+        many = tim.mismatch_seq(ag, bg, cn, tau_seq=tau)
+        assert torch.equal(one[0], many[0][:1]) and torch.equal(one[1], many[1][:1]) and torch.equal(one[2], many[2])
+        assert bool(one[1][0]) == (tau > 0)
+    p1 = tim.ppo_loss(ag, bg, adv, c1, weight=one[2])
+    pn = tim.ppo_loss(ag, bg, adv, cn, weight=one[2])
+    assert torch.equal(p1["seq_loss"], pn["seq_loss"][:1]) and torch.equal(p1["batch_loss"], p1["seq_loss"])
+    for k in ("token_loss", "contribution", "clipped"):
+        assert torch.equal(p1[k], pn[k])
