@@ -24,7 +24,8 @@
 //
 // Decode batches may run lmhead_half_partials instead: the same pass over
 //   128-entry halves of the vocab tiles, writing each half's partial where
-//   the whole-tile epilogue merges the two; the merge pairs them up again.
+//   the whole-tile epilogue merges the two; the merge pairs them up again. Up
+//   to 64 rows lmhead_half_stream forms the same partials, a wave per half.
 //
 // Kernel 2, lmhead_merge: one wavefront per row (four for launches of at most
 //   512 rows) merges that row's partials with a fixed balanced binary tree
@@ -285,6 +286,125 @@ void lmhead_half_partials(LmHeadArgs a, int n_ht, int n_tt) {
   tile_pass<NTB, WT, false, EpiPartials<false, 1>>(a, n_ht, n_tt);
 }
 
+// The same half-tile partials for batches of at most 16 NH rows, W streamed
+// through wave-private rings: one wave per half tile, no barriers.
+//
+// A wave walks its half in groups of GB W blocks of 16 entries, each over all
+// of K in stages of 64. A stage is cut into units of 16 rows x 128 bytes, 2 KB
+// of LDS: first the NH row blocks, whose operands stay in registers for the
+// stage, then the group's W blocks. The ring holds RU units; each consumed
+// unit's slot takes the unit RU further on at once, so close to the whole ring
+// is always in flight, and vmcnt (loads return in order) says when a unit has
+// landed. An accumulator takes its k-steps in ascending order as everywhere.
+//
+// Bound by HBM. What it gains over lmhead_half_partials: no stage barrier
+// drains the loads, and with 24 KB a wave all of a 150k vocabulary's 1187
+// halves are resident at once (4.6 per CU) instead of 768 and a thin second
+// round. Calls with the merge, before and after: 64 rows at d = 5120,
+// V = 152064 319 -> 291 us (5.35 TB/s of W), at d = 2560 174 -> 154, at
+// d = 4096 245 -> 239; 5 rows at d = 5120 288 -> 270. A bare stream of W
+// through the same rings takes 256 us at d = 5120 and 222 at d = 4096.
+template <int NH, int GB, int RU>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void lmhead_half_stream(LmHeadArgs a, int n_ht) {
+  constexpr int NTB = (NH + 1) / 2, NJ = 2 * NTB, U = NH + GB, NG = 8 / GB, kUnit = 16 * kRowBytes;
+  static_assert(RU > NH && 2 * RU < 64, "a stage's row blocks and a W block fit the ring; vmcnt counts it");
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[RU * kUnit + 256];
+  int* tok_lds = (int*)(lds + RU * kUnit);
+  const int lane = threadIdx.x;
+  const int64_t v0 = (int64_t)blockIdx.x * kHalfTile;
+  const int w_rows = (a.V - v0) < kHalfTile ? (int)(a.V - v0) : kHalfTile;
+  const rsrc_t wr = make_rsrc((const __bf16*)a.w + v0 * a.d, (uint64_t)w_rows * a.d * 2);
+  const rsrc_t hr = make_rsrc(a.hidden, (uint64_t)a.rows * a.d * 2);
+  const int nk = a.d / kKS;
+
+  // this lane's 16 bytes of a unit's two 1 KB loads (rows 0-7 and 8-15), relative to the unit's first row
+  const int r8 = lane >> 3;
+  const uint32_t off0 = (uint32_t)(r8 * a.d + ((lane & 7) ^ swz(r8)) * 8) * 2u;
+  const uint32_t off1 = (uint32_t)((r8 + 8) * a.d + ((lane & 7) ^ swz(r8 + 8)) * 8) * 2u;
+  const uint32_t block = (uint32_t)a.d * 32u;  // bytes of 16 rows
+  // Unit x of group g's stage s (s may run into the next group's) into the slot at `buf`. The unit's rows are in the
+  // lane's offset, so rows past the operand's end lie outside its resource's range and load zeros. Past the last
+  // group: its last stage again, never used.
+  auto issue = [&](unsigned char* buf, int x, int g, int s) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const bool over = s >= nk;
+    const int gg = over && g + 1 < NG ? g + 1 : g;
+    const int ss = !over ? s : g + 1 < NG ? s - nk : nk - 1;
+    const uint32_t o = (uint32_t)(x < NH ? x : gg * GB + x - NH) * block;
+    const int soff = ss * kRowBytes;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(x < NH ? hr : wr, (lds_void*)buf, 16, off0 + o, soff, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(x < NH ? hr : wr, (lds_void*)(buf + 1024), 16, off1 + o, soff, 0, 0);
+#endif
+  };
+  auto fence = [] {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+  };
+#if defined(__HIP_DEVICE_COMPILE__)
+  // the rows' tokens, landed before the first units (lanes past the batch read zeros, never used)
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(a.tokens, (uint64_t)a.rows * 4), (lds_void*)tok_lds, 4,
+                                           (uint32_t)lane * 4u, 0, 0, 0);
+#endif
+#pragma unroll
+  for (int u = 0; u < RU; ++u) issue(lds + u * kUnit, u % U, 0, u / U);
+
+  f32x4 acc[8][NJ];
+#pragma unroll
+  for (int bi = 0; bi < 8; ++bi)
+#pragma unroll
+    for (int bj = 0; bj < NJ; ++bj) acc[bi][bj] = f32x4{};
+  bf16x8 fb[2][NH], fa[2][2];
+  int slot = 0;  // the next unit's
+  auto next = [](int p) { return p + kUnit == RU * kUnit ? 0 : p + kUnit; };
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+#pragma unroll 1
+    for (int s = 0; s < nk; ++s) {
+      // the stage's row blocks and its first W block
+      fence();
+      wait_vmem<2 * (RU - NH - 1)>();
+      fence();
+      const int first = slot;
+#pragma unroll
+      for (int bj = 0; bj < NH; ++bj, slot = next(slot))
+#pragma unroll
+        for (int k = 0; k < 2; ++k) fb[k][bj] = read_operand(lds + slot, lane & 15, k, lane);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) fa[0][k] = read_operand(lds + slot, lane & 15, k, lane);
+      slot = first;
+#pragma unroll
+      for (int bi = 0; bi < GB; ++bi) {
+        fence();
+        wait_lgkm0_vmem<63>();  // unit bi (and the row blocks) in registers, the slots free
+        fence();
+        if (bi == 0) {
+#pragma unroll
+          for (int bj = 0; bj < NH; ++bj, slot = next(slot)) issue(lds + slot, (bj + RU) % U, g, s + (bj + RU) / U);
+        }
+        issue(lds + slot, (NH + bi + RU) % U, g, s + (NH + bi + RU) / U);
+        slot = next(slot);
+        if (bi + 1 < GB) {
+          fence();
+          wait_vmem<2 * (RU - 1)>();  // unit bi + 1 landed
+          fence();
+#pragma unroll
+          for (int k = 0; k < 2; ++k) fa[(bi + 1) & 1][k] = read_operand(lds + slot, lane & 15, k, lane);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+          for (int bj = 0; bj < NH; ++bj)
+            acc[g * GB + bi][bj] =
+                __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[bi & 1][k], fb[k][bj], acc[g * GB + bi][bj], 0, 0, 0);
+      }
+    }
+  }
+  wait_vmem<0>();  // no global->LDS request may outlive the workgroup
+  fence();
+  tile_epilogue<NTB, 1, false, 1>(a, n_ht, blockIdx.x, v0, 0, acc, nullptr, tok_lds, 0, lane);
+}
+
 // ---------------------------------------------------------------- merge
 
 // TW: vocabulary entries per partial (whole or half tiles)
@@ -514,10 +634,40 @@ static hipError_t launch_halves_t(const LmHeadArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// 64-row tiles (three workgroups of 2 waves of 128 x 32 per CU) up to 64
-// rows, 128-row tiles (two workgroups of 4 waves of 128 x 32 per CU: two waves
-// per SIMD) above.
+template <int NH, int GB, int RU>
+static hipError_t launch_stream_t(const LmHeadArgs& a, hipStream_t s) {
+  const int n_ht = n_half_tiles(a.V);
+  hipLaunchKernelGGL((lmhead_half_stream<NH, GB, RU>), dim3((unsigned)n_ht), dim3(64), 0, s, a, n_ht);
+  return hipGetLastError();
+}
+
+// Up to 64 rows: one wave per half with a ring of its own where they are all
+// resident at once (24 KB of LDS: six per CU), else 64-row tiles (three
+// workgroups of 2 waves of 128 x 32 per CU). 65..128 rows: 128-row tiles (two
+// workgroups of 4 waves of 128 x 32 per CU: two waves per SIMD).
+constexpr int kStreamPerCU = 6;
 hipError_t launch_partials_halves(const LmHeadArgs& a, hipStream_t s) {
+  // (33..64 rows keep a lone wave busy: with one or two of them per CU the CUs with two set the time, V = 50257 at
+  // d = 4096 100 us against 95; fewer rows of a short d likewise, 7 at d = 1024 23.2 against 22.9.)
+  const int n_ht = n_half_tiles(a.V), cus = device_cu_count();
+  if (a.rows <= 64 && n_ht <= kStreamPerCU * cus && ((a.rows <= 32 && a.d > 1024) || n_ht <= cus || n_ht > 2 * cus)) {
+    // All the waves start at the same place of their rows, so rows a power of two apart meet on the same memory
+    // channels; walking fewer rows at a time spreads them, at the price of reading the hidden block once per group.
+    // A bare stream at d = 2048 takes 144 us by 128 rows, 130 by 64, 118 by 32 and 109 by 16, at d = 4096 222 and
+    // 211 by 128 and 64; at other widths the orders are within 3%. Calls at V = 151936: d = 2048, 5 and 16 rows 140
+    // and 141 us on lmhead_half_partials, 152 and 153 by 128 rows, 130 and 131 by 32; 32 rows 143, 156 and by 64 140;
+    // 64 rows stay where they were (149; 159 by 128, 149 by 64). d = 4096, 5 rows: 234, 232, and by 64 227.
+    if (a.d == 2048) {
+      if (a.rows <= 16) return launch_stream_t<1, 2, 12>(a, s);
+      if (a.rows <= 32) return launch_stream_t<2, 4, 8>(a, s);
+    } else if (a.d >= 4096 && (a.d & (a.d - 1)) == 0 && a.rows <= 32) {
+      return a.rows <= 16 ? launch_stream_t<1, 4, 12>(a, s) : launch_stream_t<2, 4, 8>(a, s);
+    } else {
+      return a.rows <= 16   ? launch_stream_t<1, 8, 12>(a, s)
+             : a.rows <= 32 ? launch_stream_t<2, 8, 12>(a, s)
+                            : launch_stream_t<4, 8, 12>(a, s);
+    }
+  }
   return a.rows <= 64 ? launch_halves_t<1, 2>(a, s) : launch_halves_t<1, 4>(a, s);
 }
 

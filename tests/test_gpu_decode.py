@@ -306,3 +306,28 @@ def test_row_tiles_bitwise_equal(V, cuts):
     lp, H = oracle_rows(h, W, tok, tau, rows=range(0, T, 23))
     check_close("row tiles logp", ref[0], lp, TOL_LOGP, rows=range(0, T, 23))
     check_close("row tiles entropy", ref[1], H, TOL_ENT, rows=range(0, T, 23))
+
+
+@pytest.mark.parametrize("d,V", [
+    (128, 1000),      # two stages: fewer units than the ring holds; a last half of 104 entries
+    (384, 385),       # a last half of one entry
+    (2048, 1000),     # rows of 4 KB: groups of 2 W blocks up to 16 rows, of 4 up to 32, the two-wave shape above
+    (4096, 1279),     # a larger power of two: groups of 4 up to 32 rows
+    (8192, 400),
+    (5120, 700),      # no power of two: whole halves
+])
+@pytest.mark.parametrize("T", [1, 16, 17, 32, 33, 64])
+def test_half_stream_bitwise_equal(d, V, T):
+    """A decode batch of up to 64 rows with a wave per half tile: at 16, 32 and 64 rows the row blocks of a stage, at
+    each width the group of W blocks. Bitwise the two-stage calls' whole tiles, and within tolerance of the oracle."""
+    print(f"case half stream d={d} V={V} T={T}", flush=True)
+    h, W = inputs(T, d, V, seed=V + T + d)
+    tok = _tokens(T, V, seed=V + T)
+    dec, per_row = _decode(h, W, tok, 0.7)
+    assert per_row == -(-V // 128)
+    ws = torch.empty(tim.workspace_size(T, d, V, Mode.ROLLOUT), dtype=torch.uint8, device="cuda")
+    tim.logprobs_partials(h, W, tok, ws, 0.7, mode=Mode.ROLLOUT)
+    _same(dec, tim.logprobs_merge(ws, tok, V))
+    ref_lp, ref_H = oracle_rows(h, W, tok, 0.7)
+    check_close("half stream logp", dec[0], ref_lp, TOL_LOGP)
+    check_close("half stream entropy", dec[1], ref_H, TOL_ENT)
