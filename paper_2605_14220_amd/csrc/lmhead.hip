@@ -509,6 +509,18 @@ __global__ __launch_bounds__(256) void lmhead_merge_quad(const Partial* __restri
 // chunks of kFoldTiles per row into LDS with coalesced loads, the next chunk's
 // loads in flight while the first kFoldRows lanes fold the current one. With a
 // thread per row loading its own partials, 2048 rows of 594 took 302 us.
+// merge2 without branches, the same value: a row's maxima and exponentials do
+// not depend on its sums, so a run of merges computes them ahead of the sums'
+// chain (2048 rows of 594 partials: 79 us with branches, 50-56 without).
+__device__ __forceinline__ MSU merge2_flat(MSU a, MSU b) {
+  const float M = fmaxf(a.m, b.m);
+  const float da = a.m - M, db = b.m - M;
+  const float ea = exp2_hw(da * kLog2e), eb = exp2_hw(db * kLog2e);
+  const float s = a.s * ea + b.s * eb;
+  const float u = (a.u + da * a.s) * ea + (b.u + db * b.s) * eb;
+  const bool no_a = a.m == kNegInf, no_b = b.m == kNegInf;
+  return MSU{no_b ? a.m : no_a ? b.m : M, no_b ? a.s : no_a ? b.s : s, no_b ? a.u : no_a ? b.u : u};
+}
 constexpr int kFoldRows = 16;
 constexpr int kFoldTiles = 64;
 __global__ __launch_bounds__(256) void lmhead_merge_fold(const Partial* __restrict__ part,
@@ -538,10 +550,10 @@ __global__ __launch_bounds__(256) void lmhead_merge_fold(const Partial* __restri
     if (first + kFoldTiles < n_vt) fetch(first + kFoldTiles);
     if (tid < kFoldRows) {
       auto leaf = [&](int i) { const float4 q = buf[tid][i]; return MSU{q.x, q.y, q.z}; };
-      v = first == 0 ? leaf(0) : merge2(v, leaf(0));
+      v = first == 0 ? leaf(0) : merge2_flat(v, leaf(0));
       const int n = n_vt - first < kFoldTiles ? n_vt - first : kFoldTiles;
 #pragma unroll 8
-      for (int i = 1; i < n; ++i) v = merge2(v, leaf(i));
+      for (int i = 1; i < n; ++i) v = merge2_flat(v, leaf(i));
     }
     __syncthreads();
   }
