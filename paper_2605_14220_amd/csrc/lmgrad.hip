@@ -380,10 +380,10 @@ static hipError_t launch_small(const GemmArgs& a, hipStream_t s) {
 // The output tile of a product and what its rounds over the chip cost: the
 // tiles dealt to the CUs, times one round against a round of 256 x 256 tiles
 // (measured at K = 152064: 3.35 ms; 128 x 256 1.95, 128 x 128 1.25, 64 x 128
-// 0.83, 64 x 64 0.5 ms a round). The smaller the tile the more LDS and cache
-// traffic per flop, so smaller ones only win where larger ones leave CUs idle.
+// 0.83, 64 x 64 0.5 ms a round). The smaller the tile the more bytes a CU
+// fetches per flop, so smaller ones only win where larger ones leave CUs idle.
 // grad_hidden at K = 152064: 1001 rows at d = 2048 3.07 ms on 32 tiles of
-// 256 x 256, 0.67 on 256 of 64 x 128; 2000 rows at d = 4096 3.1 ms on 128
+// 256 x 256, 0.91 on 256 of 64 x 128; 2000 rows at d = 4096 3.1 ms on 128
 // tiles, 1.95 on 256 of 128 x 256; 3000 rows there stay on 192 tiles of
 // 256 x 256 (2 rounds of 128 x 256 cost more).
 struct GemmShape {

@@ -799,12 +799,13 @@ __device__ __forceinline__ void tile_pass_deep(const typename E::Args& a, int n_
 // tile of TA x BT, both dividing 256, so a tile reads a run of whole rows of
 // its operands' packed blocks. One tile per workgroup and one workgroup per CU,
 // its LDS holding as many 64-deep stages as fit, to cover the cache latency of
-// the few KB a stage brings. What bounds it is the LDS: a stage moves (TA + BT)
-// * 128 bytes in and 2 (NA + NB) KB out per wave, and the measured rounds sit
-// at about 128 bytes per cycle for all four shapes used (128 x 256: 176 KB in
-// 820 ns; 64 x 128: 88 KB in 350 ns). Eight waves of fewer blocks were faster
-// than four of more (128 x 128: 1.25 against 1.45 ms at K = 152064), which
-// leave one wave per SIMD and nothing to issue while it waits.
+// the few KB a stage brings. What bounds it is what one CU fetches: 70-90 GB/s
+// whatever the tile and however many of them run (a stage of 64 x 128 takes
+// 270-300 ns on 64 CUs as on 256, one of 64 x 64 180-190). Eight waves of
+// fewer blocks were faster than four of more (128 x 128: 1.25 against 1.45 ms
+// at K = 152064), which leave one wave per SIMD and nothing to issue while it
+// waits. Refilling a buffer a stage later, without the wait for the reads
+// before the barrier, and other groups of the tile order measured the same.
 template <int NV, int WT, int NA, int NB>
 struct SmallTile {
   static constexpr int NW = NV * WT;
