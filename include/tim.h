@@ -159,12 +159,14 @@ tim_status tim_logprobs_noalloc(const void* hidden, const void* w_vocab, const i
  * gives exactly the outputs of tim_logprobs_partials followed by
  * tim_logprobs_merge (whose partials are always per whole tile).
  *
- * tim_logprobs_partials: one launch over all T rows (no micro-batching; mode
- * changes nothing here). Writes T * ceil(V / TIM_VOCAB_TILE) partials of
- * 16 bytes (running max, sum of exponentials, sum of exponential-weighted
- * logit offsets, gathered token logit) into `workspace`, which must hold
- * tim_logprobs_workspace_size(T, d, V, TIM_MODE_ROLLOUT, 0) bytes. Arguments
- * and errors as tim_logprobs.
+ * tim_logprobs_partials: one launch over all T rows in either mode (no
+ * micro-batching, and no cap on the launch's rows). Writes
+ * T * ceil(V / TIM_VOCAB_TILE) partials of 16 bytes (running max, sum of
+ * exponentials, sum of exponential-weighted logit offsets, gathered token
+ * logit) into `workspace`, which must hold that many bytes -- in
+ * TIM_MODE_ROLLOUT tim_logprobs_workspace_size(T, d, V, TIM_MODE_ROLLOUT, 0),
+ * which is as many and enough in both modes, more where T <= 128. Arguments
+ * and errors otherwise as tim_logprobs.
  *
  * tim_logprobs_merge: reduces those partials to logp / entropy / lse (same
  * definitions as tim_logprobs). `tokens`, T, V and `order` must be the ones

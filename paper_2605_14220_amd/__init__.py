@@ -231,7 +231,8 @@ def logprobs_partials(hidden: torch.Tensor, w_vocab: torch.Tensor, tokens: torch
                       workspace: torch.Tensor, temperature: float = 1.0, mode: Mode = Mode.TRAINING,
                       order: Order = Order.INVARIANT):
     """First stage of logprobs over all rows in one launch: per-(row, vocab tile)
-    partials written into `workspace` (see include/tim.h)."""
+    partials written into `workspace`, which holds all T rows': workspace_size(T, d, V, Mode.ROLLOUT)
+    bytes are enough in both modes (see include/tim.h)."""
     lib = load_library()
     _require_gpu(hidden, w_vocab, tokens, workspace)
     T, d = hidden.shape

@@ -137,8 +137,7 @@ tim_status tim_logprobs_partials(const void* hidden, const void* w_vocab, const 
                                  int64_t T, int32_t d, int32_t V, float temperature, int32_t mode,
                                  int32_t order, void* workspace, size_t workspace_bytes,
                                  hipStream_t stream) {
-  const tim_status st = tim::validate_logprobs(hidden, w_vocab, tokens, T, d, V, temperature, mode, 0,
-                                               order, /*logp=*/(const float*)workspace, workspace,
+  const tim_status st = tim::validate_partials(hidden, w_vocab, tokens, T, d, V, temperature, mode, order, workspace,
                                                workspace_bytes);
   if (st != TIM_OK || T == 0) return st;
   const bool splitk4 = order == TIM_ORDER_SPLITK4;

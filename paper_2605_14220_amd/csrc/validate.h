@@ -90,6 +90,18 @@ inline tim_status validate_logprobs(const void* hidden, const void* w, const int
   return TIM_OK;
 }
 
+// tim_logprobs_partials: one launch over all T rows in either mode, so the
+// workspace holds T rows of whole-tile partials also where a training call's
+// launches have fewer rows; rollout mode asks for its call's workspace.
+inline tim_status validate_partials(const void* hidden, const void* w, const int32_t* tokens, int64_t T, int32_t d,
+                                    int32_t V, float temperature, int32_t mode, int32_t order, const void* ws,
+                                    size_t ws_bytes) {
+  const tim_status s = validate_logprobs(hidden, w, tokens, T, d, V, temperature, mode, 0, order,
+                                         /*logp=*/(const float*)ws, ws, ws_bytes);
+  if (s != TIM_OK || T == 0) return s;
+  return ws_bytes < (size_t)T * (size_t)n_tiles_of(V) * 16u ? TIM_ERR_WORKSPACE : TIM_OK;
+}
+
 // tim_logprobs_noalloc: the arguments, then whether its partials fit the
 // device scratch array (checked before the array's address is looked up).
 inline tim_status validate_logprobs_noalloc(const void* hidden, const void* w, const int32_t* tokens,

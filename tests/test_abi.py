@@ -312,6 +312,19 @@ def test_partials_rejects(lib, kw, expect):
                                      a["mode"], a["order"], a["ws"], a["ws_bytes"], None) == expect
 
 
+@pytest.mark.parametrize("T,d,V", [(20011, 5120, 152064), (8193, 8192, 300), (16385, 4096, 151936)])
+@pytest.mark.parametrize("mode", list(Mode))
+def test_partials_workspace_holds_every_row(lib, T, d, V, mode):
+    """tim_logprobs_partials is one launch over all T rows in both modes, so a workspace for the rows of one training
+    launch (tim_logprobs_workspace_size in training mode) is refused above that many rows, as is one partial less
+    than all T rows' (V tiles of 16 bytes a row)."""
+    whole = T * math.ceil(V / 256) * 16
+    assert tim.workspace_size(T, d, V, Mode.ROLLOUT) == whole > tim.workspace_size(T, d, V, Mode.TRAINING)
+    for ws_bytes in (tim.workspace_size(T, d, V, Mode.TRAINING), whole - 16):
+        assert lib.tim_logprobs_partials(FAKE, FAKE, FAKE, T, d, V, 1.0, int(mode), 0, FAKE, ws_bytes,
+                                         None) == Status.ERR_WORKSPACE
+
+
 def test_python_binding_rejects_cpu_tensors():
     import torch
     h = torch.zeros(4, 256, dtype=torch.bfloat16)
