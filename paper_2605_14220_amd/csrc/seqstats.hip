@@ -6,9 +6,12 @@
 //
 // One workgroup per response: the token terms in fp64, summed in response_sum's
 // order, which depends only on the response's length, so a response's score is
-// bitwise the same wherever it sits in the stream. The token weights are
-// written in the same pass as if the response were kept, and zeroed after it
-// where it is not.
+// bitwise the same wherever it sits in the stream. The token weights follow in
+// a second pass over the tokens (the first left them in the cache): a rejected
+// response then forms no exponentials for weights that become zero, and a call
+// without weights none at all. Written in the first pass instead, 2000
+// responses of 4000 tokens took 26 us rejected (16 here) and 18 us without
+// weights (13).
 
 #include "kernels.h"
 
@@ -28,7 +31,6 @@ __global__ __launch_bounds__(G * kChains) void seqstats_kernel(const float* __re
   s1 = s1 < s0 ? s0 : (s1 > T ? T : s1);
   const double S = response_sum<G>(s0, s1, [&](int64_t t) {
     const double delta = (double)a[t] - (double)b[t];  // exact in fp64
-    if (weight) weight[t] = tis_weight(delta, C);      // tim_mismatch's correction ratio and truncation
     return k3 ? k3_of_delta(delta) : -delta;           // K3 = (r - 1) - log r, K1 = -log r; r = e^delta
   });
   const bool k = S <= tau_seq;  // a NaN score rejects
@@ -36,8 +38,29 @@ __global__ __launch_bounds__(G * kChains) void seqstats_kernel(const float* __re
     if (score) score[j] = S;
     if (keep) keep[j] = k ? 1 : 0;
   }
-  if (weight && !k)  // each thread the tokens it wrote
-    for (int64_t t = s0 + threadIdx.x; t < s1; t += G * kChains) weight[t] = 0.f;
+  if (!weight) return;
+  constexpr int kStep = G * kChains;
+  int64_t t = s0 + threadIdx.x;
+  if (!k) {
+    for (; t < s1; t += kStep) weight[t] = 0.f;
+    return;
+  }
+  // kAhead tokens' loads issued together: 64 kept responses of 16384 tokens 26 us on one block of threads, 36 a token
+  // at a time. `full`: all of them are the response's; else (the last, once) a load past its end takes the first one's.
+  constexpr int kAhead = 4;
+  auto weights = [&](bool full) {
+    double delta[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const int64_t u = full || t + i * kStep < s1 ? t + i * kStep : t;
+      delta[i] = (double)a[u] - (double)b[u];
+    }
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i)
+      if (full || t + i * kStep < s1) weight[t + i * kStep] = tis_weight(delta[i], C);  // tim_mismatch's, truncated
+  };
+  for (; t + (kAhead - 1) * kStep < s1; t += kAhead * kStep) weights(true);
+  if (t < s1) weights(false);
 }
 
 }  // namespace

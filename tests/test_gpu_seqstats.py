@@ -153,3 +153,35 @@ def test_blocks_of_threads_agree(L):
     assert torch.equal(p1["seq_loss"], pn["seq_loss"][:1]) and torch.equal(p1["batch_loss"], p1["seq_loss"])
     for k in ("token_loss", "contribution", "clipped"):
         assert torch.equal(p1[k], pn[k])
+
+
+@pytest.mark.parametrize("est", [Estimator.K1, Estimator.K3])
+def test_rejected_responses_cost_no_weights(est):
+    """A rejected response's weights are zero whatever its tokens, so a stream of rejected responses forms no
+    correction ratios: it takes well under the time of the same stream kept (0.6 of it; 1.0 or more if the ratios
+    were formed first and zeroed after)."""
+    n, L = 16000, 2000
+    print(f"case rejected K{int(est)}", flush=True)
+    b = -torch.rand(n * L, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    a = b + 1e-3
+    cu = torch.arange(n + 1, device="cuda") * L
+    out = (torch.empty(n, dtype=torch.float64, device="cuda"), torch.empty(n, dtype=torch.uint8, device="cuda"),
+           torch.empty(n * L, device="cuda"))
+
+    def best(tau):
+        times = []
+        for _ in range(10):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(4):
+                tim.mismatch_seq(a, b, cu, tau_seq=tau, estimator=est, out=out)
+            e1.record()
+            e1.synchronize()
+            times.append(e0.elapsed_time(e1))
+        assert bool(out[1].all()) == (tau > 0) and bool((out[2] == 0).all()) == (tau < 0)
+        return min(times)
+
+    best(1e9)
+    kept, rejected = best(1e9), best(-1e9)
+    print(f"  kept {kept * 250:.1f} us, rejected {rejected * 250:.1f} us a call", flush=True)
+    assert rejected < 0.85 * kept
