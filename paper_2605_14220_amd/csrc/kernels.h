@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "plan.h"
+
 namespace tim {
 
 constexpr int kVocabTile = 256;   // vocabulary entries per softmax partial
@@ -112,7 +114,6 @@ __device__ __forceinline__ float tis_weight(double d, float C) {
 // the first 256 threads, which add them in the same order, so the same bits.
 // The terms' fp64 exponentials are long dependent chains; one wave per SIMD
 // (G = 1) leaves their latency open.
-constexpr int kChains = 256;
 template <int G, class Term>
 __device__ __forceinline__ double response_sum(int64_t s0, int64_t s1, Term term) {
   __shared__ double terms[2][G > 1 ? G * kChains : 1];
@@ -142,12 +143,8 @@ __device__ __forceinline__ double response_sum(int64_t s0, int64_t s1, Term term
   return (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
 }
 
-// Blocks of 256 threads per response of T / n_seq tokens on average: four where
-// that is more than two blocks' tokens. Sequence scores and PPO loss, one block
-// against four: 64 responses of 512..4096 tokens 9.6 -> 7.0 and 11.0 -> 7.0 us,
-// 8 of 16384 29.9 -> 18.8 and 34.6 -> 18.8; 200 of 100..800, where most of the
-// threads would have no token, stay on one (4.4 and 4.7 us).
-inline int response_blocks(int64_t T, int64_t n_seq) { return T / n_seq > 2 * kChains ? 4 : 1; }
+// Compute units of the current device (0 when there is none).
+int device_cu_count();
 
 int n_vocab_tiles(int V);
 int n_half_tiles(int V);

@@ -38,6 +38,8 @@
 // partials are then merged, lower vocabulary half first.
 
 
+#include <atomic>
+
 #include "tilepass.h"
 
 namespace tim {
@@ -566,6 +568,23 @@ __global__ __launch_bounds__(256) void lmhead_merge_fold(const Partial* __restri
 }
 
 }  // namespace
+
+// Compute units of the current device (cached per device).
+int device_cu_count() {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 0;
+  // atomic: host threads may launch on one device at once (a racing first
+  // call only queries the same attribute twice)
+  static std::atomic<int> cache[64];
+  if (dev < 64) {
+    const int c = cache[dev].load(std::memory_order_relaxed);
+    if (c > 0) return c;
+  }
+  int n = 0;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+  if (dev < 64) cache[dev].store(n, std::memory_order_relaxed);
+  return n;
+}
 
 int n_vocab_tiles(int V) { return (V + kVocabTile - 1) / kVocabTile; }
 int n_half_tiles(int V) { return (V + kHalfTile - 1) / kHalfTile; }

@@ -60,7 +60,7 @@ hipError_t launch_ppo_loss(const float* logp, const float* logp_old, const float
   if (n_seq <= 0) return hipSuccess;
   if (n_seq > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 g((unsigned)n_seq);
-  if (response_blocks(T, n_seq) > 1)
+  if (response_blocks(ResponseTerm::kPpo, T, n_seq, device_cu_count()) > 1)
     hipLaunchKernelGGL(ppo_kernel<4>, g, dim3(4 * kChains), 0, s, logp, logp_old, advantages, weight, T, cu_seqlens, p,
                        seq_loss, token_loss, grad, contrib, clipped);
   else

@@ -71,7 +71,7 @@ hipError_t launch_mismatch_seq(const float* a, const float* b, int64_t T, const 
   if (n_seq <= 0) return hipSuccess;
   if (n_seq > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 g((unsigned)n_seq);
-  if (response_blocks(T, n_seq) > 1)
+  if (response_blocks(k3 ? ResponseTerm::kK3 : ResponseTerm::kK1, T, n_seq, device_cu_count()) > 1)
     hipLaunchKernelGGL(seqstats_kernel<4>, g, dim3(4 * kChains), 0, s, a, b, T, cu_seqlens, k3 ? 1 : 0, C, tau_seq,
                        score, keep, weight);
   else

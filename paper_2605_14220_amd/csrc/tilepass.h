@@ -20,7 +20,6 @@
 // finished tile (softmax partials, logit gradients, plain fp32 stores).
 #pragma once
 
-#include <atomic>
 
 #include "kernels.h"
 
@@ -937,22 +936,5 @@ __device__ __forceinline__ void tile_pass_small(const GemmArgs& a, int n_at, int
 }
 
 }  // namespace
-
-// Compute units of the current device (cached per device).
-static int device_cu_count() {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 0;
-  // atomic: host threads may launch on one device at once (a racing first
-  // call only queries the same attribute twice)
-  static std::atomic<int> cache[64];
-  if (dev < 64) {
-    const int c = cache[dev].load(std::memory_order_relaxed);
-    if (c > 0) return c;
-  }
-  int n = 0;
-  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  if (dev < 64) cache[dev].store(n, std::memory_order_relaxed);
-  return n;
-}
 
 }  // namespace tim
