@@ -32,7 +32,8 @@ __global__ __launch_bounds__(G * kChains) void ppo_kernel(const float* __restric
     const double a = (double)adv[t];
     const double w = wt ? (double)wt[t] : 1.0;
     const double r = exp(delta);
-    const bool clip = (a > 0.0 && delta > p.hi_threshold) || (a < 0.0 && delta < p.lo_threshold);
+    // bitwise: as branches on the lanes' values the loop took 2-5% longer (256 responses of 16384 tokens 41.3 -> 43.0 us)
+    const bool clip = ((a > 0.0) & (delta > p.hi_threshold)) | ((a < 0.0) & (delta < p.lo_threshold));
     const double L = clip ? -a * (a > 0.0 ? p.clip_hi : p.clip_lo) : -a * r;
     const double tl = w * L;
     if (token_loss) token_loss[t] = (float)tl;

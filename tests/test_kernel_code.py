@@ -1,0 +1,52 @@
+"""The gfx950 code of inner loops whose source form once compiled into something slower with the same results: the
+kernels are compiled to assembly here and their loops' instructions counted. (hipcc needs no GPU for this.)"""
+
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2605_14220_amd.build import CSRC, FLAGS, HIPCC, INCLUDE
+
+
+@pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
+    done = {}
+
+    def compile_(name):
+        if name not in done:
+            out = str(tmp_path_factory.mktemp("asm") / f"{name}.s")
+            flags = [f for f in FLAGS if f not in ("-shared", "-fPIC")]
+            subprocess.run([HIPCC, *flags, "-I", INCLUDE, "-I", CSRC, "--cuda-device-only", "-S",
+                            os.path.join(CSRC, f"{name}.hip"), "-o", out], check=True, capture_output=True)
+            done[name] = open(out).read().splitlines()
+        return done[name]
+
+    return compile_
+
+
+def _loops(lines, kernel):
+    """The instruction names of every loop (a backward branch and all from its target) of the kernel whose mangled
+    name holds `kernel`, the shortest first."""
+    start = next(i for i, l in enumerate(lines) if re.match(r"_Z\S*:", l) and kernel in l.split(":")[0])
+    end = next(i for i in range(start, len(lines)) if lines[i].startswith(".Lfunc_end"))
+    body = lines[start:end]
+    label = {m[1]: i for i, l in enumerate(body) if (m := re.match(r"(\.LBB\w+):", l))}
+    loops = []
+    for i, l in enumerate(body):
+        m = re.search(r"s_c?branch\w* (\.LBB\w+)", l)
+        if m and label.get(m[1], i) < i:
+            loops.append([x.split()[0] for x in body[label[m[1]]:i + 1] if re.match(r"\t[a-z]", x)])
+    return sorted(loops, key=len)
+
+
+@pytest.mark.parametrize("blocks", [1, 4])
+def test_ppo_clip_is_no_branch(assembly, blocks):
+    """A token's clip decision is arithmetic on the lanes' values: no lane is masked off inside the token loop but
+    for the tokens past the response's end (which, with four blocks of threads, the loop tests by itself)."""
+    loops = [l for l in _loops(assembly("ppo"), f"ppo_kernelILi{blocks}E") if any("_f64" in x for x in l)]
+    assert loops
+    masks = sum(x.startswith("s_and_saveexec") for x in loops[0])
+    print(f"{blocks} block(s): {len(loops[0])} instructions, {masks} masked regions")
+    assert masks == (0 if blocks == 1 else 2)
