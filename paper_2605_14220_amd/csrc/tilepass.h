@@ -323,7 +323,11 @@ __device__ __forceinline__ bf16x8 read_b(const unsigned char* buf, int s, int bj
 // One k-step as 8 * NJ scheduling units, each pinned on its own: unit i
 // issues the MFMA of W block bi = i / NJ and row block bj, which goes up and
 // down in turn, so that every unit changes only one of its two operands from
-// the last (the pass runs at the power limit: 0.5-1% faster than bj = i % NJ).
+// the last (the pass runs at the power limit: 20011 rows at d = 4096 1.2%
+// faster than bj = i % NJ, 2100 rows on the split-K4 engine 3%). Not on the
+// 64-row tile of four waves: hipcc then keeps the split-K4 engine's second
+// accumulator set in AGPRs and moves 16 accumulators through them at every
+// stage (100 rows at d = 4096, V = 1000: 41 -> 55 us).
 // (The accumulation order of every logit is the k-step order; the order of the
 // units only interleaves independent chains.) Then, with LOAD, its share of
 // the DMA loads of a stage request into `lb` (spread evenly over the units,
@@ -341,11 +345,12 @@ __device__ __forceinline__ void kstep(bf16x8 (&fa)[2][8], bf16x8 (&fb)[2][2 * NT
   constexpr int NM = 8 * NJ;
   constexpr int L = LoadPlan<NTB, WT, NV>::L;
   constexpr int PA = AD ? P : 0, PN = AD ? (P ^ 1) : 0;
+  constexpr bool kTurn = !(NTB == 1 && WT == 2);
   static_assert(L <= NM, "at most one DMA load per unit");
   static_assert(SP == 0 || SP * (L - 1) < NM, "the spaced loads fit in the k-step");
 #pragma unroll
   for (int i = 0; i < NM; ++i) {
-    const int bi = i / NJ, bq = i % NJ, bj = (bi & 1) ? NJ - 1 - bq : bq;
+    const int bi = i / NJ, bq = i % NJ, bj = (kTurn && (bi & 1)) ? NJ - 1 - bq : bq;
     acc[bi][bj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[PA][bi], fb[P][bj], acc[bi][bj], 0, 0, 0);
     if (LOAD) {  // load q goes with unit q * NM / L, or q * SP
       if constexpr (SP > 0) {

@@ -50,3 +50,15 @@ def test_ppo_clip_is_no_branch(assembly, blocks):
     masks = sum(x.startswith("s_and_saveexec") for x in loops[0])
     print(f"{blocks} block(s): {len(loops[0])} instructions, {masks} masked regions")
     assert masks == (0 if blocks == 1 else 2)
+
+
+@pytest.mark.parametrize("shape", ["ILi1ELi2ELb1ELb0E", "ILi1ELi2ELb1ELb1E", "ILi1ELi4ELb1ELb0E", "ILi1ELi4ELb0ELb0E",
+                                   "ILi2ELi4ELb0ELb0E"])
+def test_k_loop_moves_no_accumulators(assembly, shape):
+    """The stage loop of the head's tile pass (row blocks, waves along the rows, split-K4, logits dump) issues its 32
+    or 64 MFMAs a wave on accumulators that stay where they are: none is copied between the register files."""
+    loop = next(l for l in _loops(assembly("lmhead"), f"lmhead_partials{shape}") if any("mfma" in x for x in l))
+    mfma = sum("mfma" in x for x in loop)
+    moves = sum(x.startswith("v_accvgpr") for x in loop)
+    print(f"{shape}: {mfma} MFMAs, {moves} accumulator moves, {len(loop)} instructions")
+    assert mfma in (32, 64) and moves == 0
