@@ -739,11 +739,18 @@ static hipError_t launch_merge_tree(const Partial* part, const int32_t* tokens, 
 hipError_t launch_merge(const Partial* part, const int32_t* tokens, int64_t rows, int V,
                         bool left_fold, float* logp, float* entropy, float* lse, hipStream_t s) {
   if (left_fold) {
-    const int64_t nb = (rows + kFoldRows - 1) / kFoldRows;
-    if (nb > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(lmhead_merge_fold, dim3((unsigned)nb), dim3(256), 0, s, part, tokens, rows,
-                       n_vocab_tiles(V), V, logp, entropy, lse);
-    return hipGetLastError();
+    // 16 threads a row: 2^27 rows per launch, as a grid holds fewer than 2^32 threads
+    constexpr int64_t kRows = (int64_t)1 << 27;
+    const int n_vt = n_vocab_tiles(V);
+    for (int64_t r = 0; r < rows; r += kRows) {
+      const int64_t n = rows - r < kRows ? rows - r : kRows;
+      hipLaunchKernelGGL(lmhead_merge_fold, dim3((unsigned)((n + kFoldRows - 1) / kFoldRows)), dim3(256), 0, s,
+                         part + r * n_vt, tokens + r, n, n_vt, V, logp + r, entropy ? entropy + r : nullptr,
+                         lse ? lse + r : nullptr);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   }
   return launch_merge_tree<false>(part, tokens, rows, V, logp, entropy, lse, s);
 }

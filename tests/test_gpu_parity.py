@@ -223,6 +223,20 @@ def test_splitk4_row_tiles_agree(T, d, V):
     check_close("splitk4 entropy", one[1], ref_H, TOL_ENT)
 
 
+def test_splitk4_merge_of_many_rows():
+    """The split-K4 merge of 2^28 + 5 rows of one tile (more threads, at 16 a row, than one grid holds): the closed
+    form of two equal logits in every row, the last ones' tokens out of range."""
+    T, V = (1 << 28) + 5, 2
+    print(f"case splitk4 merge T={T}", flush=True)
+    part = torch.tensor([0.5, 2.0, 0.0, 0.5], device="cuda").repeat(T, 1)  # max, sum, weighted sum, token's logit
+    tok = torch.zeros(T, dtype=torch.int32, device="cuda")
+    tok[T - 3:] = V
+    lp = torch.zeros(T, device="cuda")
+    tim.logprobs_merge(part, tok, V, order=Order.SPLITK4, out=(lp, None, None))
+    assert torch.isnan(lp[T - 3:]).all()
+    assert (lp[:T - 3] + float(np.log(2.0))).abs().max().item() < 1e-6
+
+
 @pytest.mark.parametrize("V,mode", [(4096, Mode.TRAINING), (1000, Mode.TRAINING), (4096, Mode.ROLLOUT),
                                     (151936, Mode.ROLLOUT)])
 def test_duplicated_vocabulary_shifts_by_log2(V, mode):
