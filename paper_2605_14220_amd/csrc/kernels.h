@@ -143,6 +143,11 @@ __device__ __forceinline__ double response_sum(int64_t s0, int64_t s1, Term term
   return (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
 }
 
+// Responses per launch: a grid holds fewer than 2^32 threads (a launch of more
+// succeeds with the count wrapped), and a response has 256 (1024 only where
+// there are few).
+constexpr int64_t kLaunchResponses = (int64_t)1 << 23;
+
 // Compute units of the current device (0 when there is none).
 int device_cu_count();
 

@@ -339,8 +339,7 @@ __global__ __launch_bounds__(256) void grad_coef_kernel(const float* __restrict_
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(float* __restrict__ p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0.f;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0.f;
 }
 
 }  // namespace
@@ -465,8 +464,7 @@ hipError_t launch_grad_coef(const float* lse, const float* entropy, const float*
 
 hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  const int64_t nb = (n + 255) / 256;
-  if (nb > 0x7fffffff) return hipErrorInvalidValue;
+  const int64_t nb = std::min<int64_t>((n + 255) / 256, (int64_t)1 << 20);
   hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)nb), dim3(256), 0, s, p, n);
   return hipGetLastError();
 }

@@ -710,7 +710,7 @@ hipError_t launch_partials_halves(const LmHeadArgs& a, hipStream_t s) {
 constexpr int64_t kQuadMergeRows = 512;
 
 template <bool HALVES>
-static hipError_t launch_merge_tree(const Partial* part, const int32_t* tokens, int64_t rows, int V, float* logp,
+static hipError_t launch_merge_rows(const Partial* part, const int32_t* tokens, int64_t rows, int V, float* logp,
                                     float* entropy, float* lse, hipStream_t s) {
   const int n_vt = n_vocab_tiles(V);
   const dim3 b(256);
@@ -723,9 +723,7 @@ static hipError_t launch_merge_tree(const Partial* part, const int32_t* tokens, 
     else return hipErrorInvalidValue;
     return hipGetLastError();
   }
-  const int64_t nb = (rows + 3) / 4;
-  if (nb > 0x7fffffff) return hipErrorInvalidValue;
-  const dim3 g((unsigned)nb);
+  const dim3 g((unsigned)((rows + 3) / 4));
   if (n_vt <= 64) hipLaunchKernelGGL((lmhead_merge_tree<1, HALVES>), g, b, 0, s, part, tokens, rows, n_vt, V, logp, entropy, lse);
   else if (n_vt <= 128) hipLaunchKernelGGL((lmhead_merge_tree<2, HALVES>), g, b, 0, s, part, tokens, rows, n_vt, V, logp, entropy, lse);
   else if (n_vt <= 256) hipLaunchKernelGGL((lmhead_merge_tree<4, HALVES>), g, b, 0, s, part, tokens, rows, n_vt, V, logp, entropy, lse);
@@ -736,21 +734,38 @@ static hipError_t launch_merge_tree(const Partial* part, const int32_t* tokens, 
   return hipGetLastError();
 }
 
+// A grid holds fewer than 2^32 threads (a launch of more succeeds with the
+// count wrapped), and the merges take 64 or 16 threads a row: 2^25 rows per launch.
+constexpr int64_t kMergeRows = (int64_t)1 << 25;
+template <class F>
+static hipError_t merge_chunks(int64_t rows, F launch) {
+  for (int64_t r = 0; r < rows; r += kMergeRows) {
+    const hipError_t e = launch(r, rows - r < kMergeRows ? rows - r : kMergeRows);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+template <bool HALVES>
+static hipError_t launch_merge_tree(const Partial* part, const int32_t* tokens, int64_t rows, int V, float* logp,
+                                    float* entropy, float* lse, hipStream_t s) {
+  const int per_row = HALVES ? n_half_tiles(V) : n_vocab_tiles(V);
+  return merge_chunks(rows, [&](int64_t r, int64_t n) {
+    return launch_merge_rows<HALVES>(part + r * per_row, tokens + r, n, V, logp + r, entropy ? entropy + r : nullptr,
+                                     lse ? lse + r : nullptr, s);
+  });
+}
+
 hipError_t launch_merge(const Partial* part, const int32_t* tokens, int64_t rows, int V,
                         bool left_fold, float* logp, float* entropy, float* lse, hipStream_t s) {
   if (left_fold) {
-    // 16 threads a row: 2^27 rows per launch, as a grid holds fewer than 2^32 threads
-    constexpr int64_t kRows = (int64_t)1 << 27;
     const int n_vt = n_vocab_tiles(V);
-    for (int64_t r = 0; r < rows; r += kRows) {
-      const int64_t n = rows - r < kRows ? rows - r : kRows;
+    return merge_chunks(rows, [&](int64_t r, int64_t n) {
       hipLaunchKernelGGL(lmhead_merge_fold, dim3((unsigned)((n + kFoldRows - 1) / kFoldRows)), dim3(256), 0, s,
                          part + r * n_vt, tokens + r, n, n_vt, V, logp + r, entropy ? entropy + r : nullptr,
                          lse ? lse + r : nullptr);
-      const hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+      return hipGetLastError();
+    });
   }
   return launch_merge_tree<false>(part, tokens, rows, V, logp, entropy, lse, s);
 }

@@ -60,15 +60,20 @@ hipError_t launch_ppo_loss(const float* logp, const float* logp_old, const float
                            hipStream_t s) {
   if (n_seq <= 0) return hipSuccess;
   if (n_seq > 0x7fffffff) return hipErrorInvalidValue;
-  const dim3 g((unsigned)n_seq);
-  if (response_blocks(ResponseTerm::kPpo, T, n_seq, device_cu_count()) > 1)
-    hipLaunchKernelGGL(ppo_kernel<4>, g, dim3(4 * kChains), 0, s, logp, logp_old, advantages, weight, T, cu_seqlens, p,
-                       seq_loss, token_loss, grad, contrib, clipped);
-  else
-    hipLaunchKernelGGL(ppo_kernel<1>, g, dim3(kChains), 0, s, logp, logp_old, advantages, weight, T, cu_seqlens, p,
-                       seq_loss, token_loss, grad, contrib, clipped);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !batch_loss) return e;
+  const bool four = response_blocks(ResponseTerm::kPpo, T, n_seq, device_cu_count()) > 1;
+  for (int64_t j = 0; j < n_seq; j += kLaunchResponses) {
+    const dim3 g((unsigned)(n_seq - j < kLaunchResponses ? n_seq - j : kLaunchResponses));
+    double* sl = seq_loss ? seq_loss + j : nullptr;
+    if (four)
+      hipLaunchKernelGGL(ppo_kernel<4>, g, dim3(4 * kChains), 0, s, logp, logp_old, advantages, weight, T,
+                         cu_seqlens + j, p, sl, token_loss, grad, contrib, clipped);
+    else
+      hipLaunchKernelGGL(ppo_kernel<1>, g, dim3(kChains), 0, s, logp, logp_old, advantages, weight, T, cu_seqlens + j,
+                         p, sl, token_loss, grad, contrib, clipped);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (!batch_loss) return hipSuccess;
   hipLaunchKernelGGL(ppo_batch_kernel, dim3(1), dim3(kChains), 0, s, (const double*)seq_loss, n_seq, batch_loss);
   return hipGetLastError();
 }

@@ -70,14 +70,22 @@ hipError_t launch_mismatch_seq(const float* a, const float* b, int64_t T, const 
                                uint8_t* keep, float* weight, hipStream_t s) {
   if (n_seq <= 0) return hipSuccess;
   if (n_seq > 0x7fffffff) return hipErrorInvalidValue;
-  const dim3 g((unsigned)n_seq);
-  if (response_blocks(k3 ? ResponseTerm::kK3 : ResponseTerm::kK1, T, n_seq, device_cu_count()) > 1)
-    hipLaunchKernelGGL(seqstats_kernel<4>, g, dim3(4 * kChains), 0, s, a, b, T, cu_seqlens, k3 ? 1 : 0, C, tau_seq,
-                       score, keep, weight);
-  else
-    hipLaunchKernelGGL(seqstats_kernel<1>, g, dim3(kChains), 0, s, a, b, T, cu_seqlens, k3 ? 1 : 0, C, tau_seq, score,
-                       keep, weight);
-  return hipGetLastError();
+  const bool four =
+      response_blocks(k3 ? ResponseTerm::kK3 : ResponseTerm::kK1, T, n_seq, device_cu_count()) > 1;
+  for (int64_t j = 0; j < n_seq; j += kLaunchResponses) {
+    const dim3 g((unsigned)(n_seq - j < kLaunchResponses ? n_seq - j : kLaunchResponses));
+    double* sc = score ? score + j : nullptr;
+    uint8_t* kp = keep ? keep + j : nullptr;
+    if (four)
+      hipLaunchKernelGGL(seqstats_kernel<4>, g, dim3(4 * kChains), 0, s, a, b, T, cu_seqlens + j, k3 ? 1 : 0, C,
+                         tau_seq, sc, kp, weight);
+    else
+      hipLaunchKernelGGL(seqstats_kernel<1>, g, dim3(kChains), 0, s, a, b, T, cu_seqlens + j, k3 ? 1 : 0, C, tau_seq,
+                         sc, kp, weight);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace tim

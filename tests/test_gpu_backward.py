@@ -263,6 +263,17 @@ def test_grad_hidden_output_tiles_agree(T):
     _bound_check(f"grad_hidden tiles T={T}", gh.index_select(0, idx), dacc @ wf, np.abs(dacc) @ np.abs(wf), 1024)
 
 
+def test_no_tokens_clears_a_large_grad_w():
+    """T = 0 writes zeros to all of grad_w, here 2^32 + 16384 elements (more than one grid has threads)."""
+    V, d = (1 << 18) + 1, 16384
+    print(f"case clear {V} x {d}", flush=True)
+    gw = torch.full((V, d), 7.0, device="cuda")
+    st = tim.load_library().tim_logprobs_backward(None, None, None, 0, d, V, 1.0, None, None, None, None, 0, None,
+                                                  gw.data_ptr(), 0, None, 0, torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    assert not gw.any().item()
+
+
 def test_grad_w_accumulation_continues_the_chain():
     """dW(first 256 rows) then += dW(next 444 rows) is bitwise dW(all 700 rows)."""
     T, d, V, tau = 700, 128, 2000, 1.0

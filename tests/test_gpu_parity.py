@@ -223,16 +223,17 @@ def test_splitk4_row_tiles_agree(T, d, V):
     check_close("splitk4 entropy", one[1], ref_H, TOL_ENT)
 
 
-def test_splitk4_merge_of_many_rows():
-    """The split-K4 merge of 2^28 + 5 rows of one tile (more threads, at 16 a row, than one grid holds): the closed
-    form of two equal logits in every row, the last ones' tokens out of range."""
-    T, V = (1 << 28) + 5, 2
-    print(f"case splitk4 merge T={T}", flush=True)
+@pytest.mark.parametrize("order,T", [(Order.INVARIANT, (1 << 26) + 5), (Order.SPLITK4, (1 << 28) + 5)])
+def test_merge_of_many_rows(order, T):
+    """The merge of more rows of one tile than one grid has threads for (64 a row in the tree, 16 in the split-K4
+    fold): the closed form of two equal logits in every row, the last ones' tokens out of range."""
+    V = 2
+    print(f"case merge {order.name} T={T}", flush=True)
     part = torch.tensor([0.5, 2.0, 0.0, 0.5], device="cuda").repeat(T, 1)  # max, sum, weighted sum, token's logit
     tok = torch.zeros(T, dtype=torch.int32, device="cuda")
     tok[T - 3:] = V
     lp = torch.zeros(T, device="cuda")
-    tim.logprobs_merge(part, tok, V, order=Order.SPLITK4, out=(lp, None, None))
+    tim.logprobs_merge(part, tok, V, order=order, out=(lp, None, None))
     assert torch.isnan(lp[T - 3:]).all()
     assert (lp[:T - 3] + float(np.log(2.0))).abs().max().item() < 1e-6
 

@@ -185,3 +185,23 @@ def test_rejected_responses_cost_no_weights(est):
     kept, rejected = best(1e9), best(-1e9)
     print(f"  kept {kept * 250:.1f} us, rejected {rejected * 250:.1f} us a call", flush=True)
     assert rejected < 0.85 * kept
+
+
+def test_more_responses_than_a_grid_holds():
+    """2^24 + 3 responses of one token (256 threads each: more than the 2^32 threads of one grid): every score, mask
+    and weight, and the PPO loss's."""
+    n = (1 << 24) + 3
+    print(f"case {n} responses", flush=True)
+    b = -torch.rand(n, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    a = b + 0.5 * torch.randn(n, device="cuda", generator=torch.Generator(device="cuda").manual_seed(4))
+    cu = torch.arange(n + 1, device="cuda")
+    d = a.double() - b.double()
+    score, keep, w = tim.mismatch_seq(a, b, cu, tau_seq=0.1, estimator=Estimator.K1)
+    assert torch.equal(score, -d) and torch.equal(keep.bool(), -d <= 0.1)
+    want = torch.where(-d <= 0.1, torch.exp(d).clamp(max=2.0), torch.zeros_like(d))
+    assert ((w.double() - want).abs() <= 1e-6 * want).all()
+    adv = torch.ones(n, device="cuda")
+    out = tim.ppo_loss(a, b, adv, cu)
+    loss = -torch.exp(d).clamp(max=1.0 + float(np.float32(0.2)))  # positive advantages clip above only
+    assert ((out["seq_loss"] - loss).abs() <= 1e-12 * loss.abs()).all()
+    assert abs(out["batch_loss"].item() - loss.mean().item()) <= 1e-9
