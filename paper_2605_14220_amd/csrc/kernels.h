@@ -159,20 +159,23 @@ int n_half_tiles(int V);
 // smaller where the smaller tiles all fit the chip at once; it changes the
 // launch shape only.
 hipError_t launch_partials(const LmHeadArgs& a, int rows_per_wg, bool splitk4, hipStream_t s);
-// Partials of every (row, half vocabulary tile), 64 or 128 rows per row tile
-// (by the launch's row count; 2 or 4 waves of 128 x 32): part is
-// [rows, n_half_tiles]; each half's
-// partial equals the one the whole-tile epilogue merges, so
-// launch_merge_halves gives the outputs of launch_partials + launch_merge bit
-// for bit.
+// Partials of every (row, half vocabulary tile) for at most 128 rows: up to 64
+// a wave per half (stream_shape) or 64-row tiles of two waves, above 128-row
+// tiles of four. part is [rows, n_half_tiles]; each half's partial equals the
+// one the whole-tile epilogue merges, so launch_merge_halves gives the outputs
+// of launch_partials + launch_merge bit for bit.
 hipError_t launch_partials_halves(const LmHeadArgs& a, hipStream_t s);
-// Whether a decode batch of `rows` rows on the current device takes half
-// tiles. Up to 64 rows: the shape (whole tiles two per CU, or half tiles
-// three per CU) whose last round of workgroups leaves fewer slots idle; the
-// half shape re-reads the row tile once per 128 vocabulary entries instead of
-// 256, so it only pays where it evens out the rounds. 65..128 rows: always
-// (whole tiles one workgroup per CU against halves two, each of four waves).
-// Either gives the same bits.
+// Whether a launch of `rows` rows on the current device takes half tiles.
+// 65..128 rows: always (whole tiles one workgroup per CU against halves two,
+// each of four waves). Up to 64 rows: where the two-wave tiles, three
+// workgroups per CU, leave fewer slots of their last round idle than whole
+// tiles, two per CU; the halves re-read the rows once per 128 vocabulary
+// entries instead of 256. On 256 CUs that leaves V = 98305..131072 to whole
+// tiles, and the wave-per-half kernel, though it holds all those halves at
+// once, is no faster there: against whole tiles at d >= 2560, up to 32 rows,
+// V = 100352 1.02-1.09 x, 128256 0.96-1.01, 131072 0.95-1.02, 33..64 rows
+// 1.02-1.13, 0.99-1.05 and 1.0-1.04 (d = 2048 up to 16 rows 0.91, 0.89 and
+// 0.89; d <= 256 0.73-0.95). Either gives the same bits.
 bool prefer_half_tiles(int V, int64_t rows);
 hipError_t launch_merge_halves(const Partial* part, const int32_t* tokens, int64_t rows, int V, float* logp,
                                float* entropy, float* lse, hipStream_t s);

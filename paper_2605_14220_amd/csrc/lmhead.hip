@@ -303,10 +303,10 @@ void lmhead_half_partials(LmHeadArgs a, int n_ht, int n_tt) {
 // is always in flight, and vmcnt (loads return in order) says when a unit has
 // landed. An accumulator takes its k-steps in ascending order as everywhere.
 //
-// Bound by HBM. What it gains over lmhead_half_partials: no stage barrier
-// drains the loads, and with 24 KB a wave all of a 150k vocabulary's 1187
-// halves are resident at once (4.6 per CU) instead of 768 and a thin second
-// round. Calls with the merge, before and after: 64 rows at d = 5120,
+// Bound by HBM where there are enough halves (stream_shape says where it is
+// taken). What it gains over lmhead_half_partials: no stage barrier drains the
+// loads, and with 24 KB a wave all of a 150k vocabulary's 1187 halves are
+// resident at once (4.6 per CU) instead of 768 and a thin second round. Calls with the merge, before and after: 64 rows at d = 5120,
 // V = 152064 319 -> 291 us (5.35 TB/s of W), at d = 2560 174 -> 154, at
 // d = 4096 245 -> 239; 5 rows at d = 5120 288 -> 270. A bare stream of W
 // through the same rings takes 256 us at d = 5120 and 222 at d = 4096.
@@ -509,12 +509,6 @@ __global__ __launch_bounds__(256) void lmhead_merge_quad(const Partial* __restri
                                                 row, logp, ent, lse);
 }
 
-// SPLITK4 engine: partials folded left to right, kFoldRows rows per workgroup.
-// The fold is a serial chain of n_vt merges per row, so it is bound by that
-// chain's latency once the partials are at hand: the workgroup brings them in
-// chunks of kFoldTiles per row into LDS with coalesced loads, the next chunk's
-// loads in flight while the first kFoldRows lanes fold the current one. With a
-// thread per row loading its own partials, 2048 rows of 594 took 302 us.
 // merge2 without branches, the same value: a row's maxima and exponentials do
 // not depend on its sums, so a run of merges computes them ahead of the sums'
 // chain (2048 rows of 594 partials: 79 us with branches, 50-56 without).
@@ -527,6 +521,14 @@ __device__ __forceinline__ MSU merge2_flat(MSU a, MSU b) {
   const bool no_a = a.m == kNegInf, no_b = b.m == kNegInf;
   return MSU{no_b ? a.m : no_a ? b.m : M, no_b ? a.s : no_a ? b.s : s, no_b ? a.u : no_a ? b.u : u};
 }
+
+// SPLITK4 engine: partials folded left to right, kFoldRows rows per workgroup.
+// The fold is a serial chain of n_vt merges per row, so it is bound by that
+// chain's latency once the partials are at hand: the workgroup brings them in
+// chunks of kFoldTiles per row into LDS with coalesced loads, the next chunk's
+// loads in flight while the first kFoldRows lanes fold the current one. With a
+// thread per row loading its own partials, 2048 rows of 594 took 302 us (4
+// partials a row 0.4 us less than this).
 constexpr int kFoldRows = 16;
 constexpr int kFoldTiles = 64;
 __global__ __launch_bounds__(256) void lmhead_merge_fold(const Partial* __restrict__ part,
@@ -676,32 +678,19 @@ static hipError_t launch_stream_t(const LmHeadArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Up to 64 rows: one wave per half with a ring of its own where they are all
-// resident at once (24 KB of LDS: six per CU), else 64-row tiles (three
-// workgroups of 2 waves of 128 x 32 per CU). 65..128 rows: 128-row tiles (two
-// workgroups of 4 waves of 128 x 32 per CU: two waves per SIMD).
-constexpr int kStreamPerCU = 6;
+// Up to 64 rows: a wave per half with a ring of its own where that is the
+// faster shape (stream_shape), else 64-row tiles (three workgroups of 2 waves
+// of 128 x 32 per CU). 65..128 rows: 128-row tiles (two workgroups of 4 waves
+// of 128 x 32 per CU: two waves per SIMD).
 hipError_t launch_partials_halves(const LmHeadArgs& a, hipStream_t s) {
-  // (33..64 rows keep a lone wave busy: with one or two of them per CU the CUs with two set the time, V = 50257 at
-  // d = 4096 100 us against 95; fewer rows of a short d likewise, 7 at d = 1024 23.2 against 22.9.)
-  const int n_ht = n_half_tiles(a.V), cus = device_cu_count();
-  if (a.rows <= 64 && n_ht <= kStreamPerCU * cus && ((a.rows <= 32 && a.d > 1024) || n_ht <= cus || n_ht > 2 * cus)) {
-    // All the waves start at the same place of their rows, so rows a power of two apart meet on the same memory
-    // channels; walking fewer rows at a time spreads them, at the price of reading the hidden block once per group.
-    // A bare stream at d = 2048 takes 144 us by 128 rows, 130 by 64, 118 by 32 and 109 by 16, at d = 4096 222 and
-    // 211 by 128 and 64; at other widths the orders are within 3%. Calls at V = 151936: d = 2048, 5 and 16 rows 140
-    // and 141 us on lmhead_half_partials, 152 and 153 by 128 rows, 130 and 131 by 32; 32 rows 143, 156 and by 64 140;
-    // 64 rows stay where they were (149; 159 by 128, 149 by 64). d = 4096, 5 rows: 234, 232, and by 64 227.
-    if (a.d == 2048) {
-      if (a.rows <= 16) return launch_stream_t<1, 2, 12>(a, s);
-      if (a.rows <= 32) return launch_stream_t<2, 4, 8>(a, s);
-    } else if (a.d >= 4096 && (a.d & (a.d - 1)) == 0 && a.rows <= 32) {
-      return a.rows <= 16 ? launch_stream_t<1, 4, 12>(a, s) : launch_stream_t<2, 4, 8>(a, s);
-    } else {
-      return a.rows <= 16   ? launch_stream_t<1, 8, 12>(a, s)
-             : a.rows <= 32 ? launch_stream_t<2, 8, 12>(a, s)
-                            : launch_stream_t<4, 8, 12>(a, s);
-    }
+  const StreamShape st = stream_shape(a.rows, a.d, n_half_tiles(a.V), device_cu_count());
+  switch (st.row_blocks) {
+    case 1:
+      return st.group == 2   ? launch_stream_t<1, 2, 12>(a, s)
+             : st.group == 4 ? launch_stream_t<1, 4, 12>(a, s)
+                             : launch_stream_t<1, 8, 12>(a, s);
+    case 2: return st.group == 4 ? launch_stream_t<2, 4, 8>(a, s) : launch_stream_t<2, 8, 12>(a, s);
+    case 4: return launch_stream_t<4, 8, 12>(a, s);
   }
   return a.rows <= 64 ? launch_halves_t<1, 2>(a, s) : launch_halves_t<1, 4>(a, s);
 }
