@@ -266,54 +266,56 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_fused(const uint4* __restrict
   }
 }
 
-// Column sums of G x r over block `blk` of up to 256 rows, two columns per
-// thread; cb the workgroup's range of 512 columns. The rows go in order, or
-// with `quarters` each 64-row quarter does, as (q0 + q1) + (q2 + q3).
-__device__ __forceinline__ void dgamma_block(const uint32_t* __restrict__ x, const float* __restrict__ rstd,
-                                             const float2* __restrict__ G, int64_t T, int d, int quarters, int64_t blk,
-                                             int cb, float2* __restrict__ part) {
-  const int k = cb * 256 + threadIdx.x, d2 = d / 2;  // column pair
-  if (k >= d2) return;
+// Column sums of G x r over block `blk` of up to 256 rows, a column per thread;
+// cb the workgroup's range of 256 columns. The rows go in order, or with
+// `quarters` each 64-row quarter does, as (q0 + q1) + (q2 + q3). R rows' loads
+// are issued ahead of their terms (the adds stay in row order). A block is one
+// chain of 256 rows, so few of them are bound by its latency: two columns per
+// thread, in half as many workgroups with twice the instructions a row, were
+// 1.1-1.45 times slower up to 1000 rows and 1.05-1.25 at 5000 of d = 8192.
+template <int R>
+__device__ __forceinline__ void dgamma_block(const uint16_t* __restrict__ x, const float* __restrict__ rstd,
+                                             const float* __restrict__ G, int64_t T, int d, int quarters, int64_t blk,
+                                             int cb, float* __restrict__ part) {
+  const int k = cb * 256 + threadIdx.x;
+  if (k >= d) return;
   int64_t t = blk * 256;
   const int64_t t1 = (T - t) < 256 ? T : t + 256;
   const int chain = quarters ? 64 : 256;
-  float2 even = float2{0.f, 0.f}, total = float2{0.f, 0.f};
+  float even = 0.f, total = 0.f;
 #pragma unroll 1
   for (int q = 0; q * chain < 256; ++q) {
     const int64_t te = (t1 - t) < chain ? t1 : t + chain;
-    float2 acc = float2{0.f, 0.f};
-    auto add = [&](uint32_t xv, float2 gv, float rv) {
-      acc.x = acc.x + (gv.x * bf16_lo(xv)) * rv;
-      acc.y = acc.y + (gv.y * bf16_hi(xv)) * rv;
-    };
-    // 16 rows' loads issued ahead of their terms (the adds stay in row order)
-    for (; t + 16 <= te; t += 16) {
-      uint32_t xv[16];
-      float2 gv[16];
-      float rv[16];
+    float acc = 0.f;
+    auto rows = [&](auto n) {
+      float xv[n.value], gv[n.value], rv[n.value];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        xv[i] = x[(t + i) * d2 + k];
-        gv[i] = G[(t + i) * d2 + k];
+      for (int i = 0; i < n.value; ++i) {
+        xv[i] = bf16_lo(x[(t + i) * d + k]);
+        gv[i] = G[(t + i) * d + k];
         rv[i] = rstd[t + i];
       }
 #pragma unroll
-      for (int i = 0; i < 16; ++i) add(xv[i], gv[i], rv[i]);
-    }
-    for (; t < te; ++t) add(x[t * d2 + k], G[t * d2 + k], rstd[t]);
+      for (int i = 0; i < n.value; ++i) acc = acc + (gv[i] * xv[i]) * rv[i];
+      t += n.value;
+    };
+    while (t + R <= te) rows(std::integral_constant<int, R>{});
+    while (t + 8 <= te) rows(std::integral_constant<int, 8>{});
+    while (t < te) rows(std::integral_constant<int, 1>{});
     if (!quarters) total = acc;
     else if ((q & 1) == 0) even = acc;
-    else if (q == 1) total = float2{even.x + acc.x, even.y + acc.y};
-    else total = float2{total.x + (even.x + acc.x), total.y + (even.y + acc.y)};
+    else if (q == 1) total = even + acc;
+    else total = total + (even + acc);
   }
-  part[blk * d2 + k] = total;
+  part[blk * d + k] = total;
 }
 
-__global__ __launch_bounds__(256) void rmsnorm_dgamma_part(const uint32_t* __restrict__ x,
+template <int R>
+__global__ __launch_bounds__(256) void rmsnorm_dgamma_part(const uint16_t* __restrict__ x,
                                                            const float* __restrict__ rstd,
-                                                           const float2* __restrict__ G, int64_t T, int d,
-                                                           int quarters, float2* __restrict__ part) {
-  dgamma_block(x, rstd, G, T, d, quarters, blockIdx.y, blockIdx.x, part);
+                                                           const float* __restrict__ G, int64_t T, int d,
+                                                           int quarters, float* __restrict__ part) {
+  dgamma_block<R>(x, rstd, G, T, d, quarters, blockIdx.y, blockIdx.x, part);
 }
 
 // grad_x and grad_gamma's block sums in one launch: workgroups of 4 rows of dx
@@ -350,7 +352,7 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_both(const uint4* __restrict_
     cb = in - 64;
     if (blk >= n_blocks) return;
   }
-  dgamma_block((const uint32_t*)x, rstd, (const float2*)G, T, d, quarters, blk, cb, (float2*)part);
+  dgamma_block<32>((const uint16_t*)x, rstd, (const float*)G, T, d, quarters, blk, cb, part);
 }
 
 // dg_k (+)= the blocks' sums in block order.
@@ -375,12 +377,12 @@ __global__ __launch_bounds__(256) void rmsnorm_dgamma_final(const float* __restr
 }  // namespace
 
 // f(NCL) with NCL = d / 512 as a compile-time constant where a lane keeps its
-// chunks of the row in registers (d a multiple of 512 up to 512 MAXN), else f(0).
-template <int MAXN, int N = MAXN, class F>
+// chunks of the row in registers (d a multiple of 512 up to 512 N), else f(LAST).
+template <int N, int LAST = 0, class F>
 static void with_chunks(int d, F f) {
-  if constexpr (N == 0) f(std::integral_constant<int, 0>{});
+  if constexpr (N == LAST) f(std::integral_constant<int, LAST>{});
   else if (d == 512 * N) f(std::integral_constant<int, N>{});
-  else with_chunks<MAXN, N - 1>(d, f);
+  else with_chunks<N - 1, LAST>(d, f);
 }
 constexpr int kFwdChunks = 16, kBwdChunks = 10;  // as many as the registers hold
 static bool keeps_row(int d) { return d % 512 == 0 && d <= 512 * kBwdChunks; }
@@ -437,7 +439,7 @@ hipError_t launch_rmsnorm_backward(const void* x, const void* gamma, const float
     if (e != hipSuccess) return e;
   }
   const int64_t n_blocks = fused ? (T + 4 * rpw - 1) / (4 * rpw) : (T + 255) / 256;
-  const unsigned n_cb = (unsigned)((d + 511) / 512);  // workgroups of 512 columns
+  const unsigned n_cb = (unsigned)((d + 255) / 256);  // workgroups of 256 columns
   if (grad_gamma && n_blocks > 65535) return hipErrorInvalidValue;
   if (T > 0 && !fused && (grad_x || grad_gamma)) {
     const dim3 b(256);
@@ -451,7 +453,7 @@ hipError_t launch_rmsnorm_backward(const void* x, const void* gamma, const float
     if (both) {
       const int64_t nb = n_blocks * (64 + n_cb) + std::min<int64_t>(n_blocks, kLead) * n_cb;
       if (nb > 0x7fffffff) return hipErrorInvalidValue;
-      with_chunks<kBwdChunks>(d, [&](auto n) {
+      with_chunks<kBwdChunks, 1>(d, [&](auto n) {  // (keeps_row)
         hipLaunchKernelGGL(rmsnorm_bwd_both<n.value>, dim3((unsigned)nb), b, 0, s, xp, gp, rstd, Gp, T, d, (int)n_cb,
                            quarters, dxp, part);
       });
@@ -463,9 +465,13 @@ hipError_t launch_rmsnorm_backward(const void* x, const void* gamma, const float
           hipLaunchKernelGGL(rmsnorm_bwd_x<n.value>, dim3((unsigned)nb), b, 0, s, xp, gp, rstd, Gp, T, d, dxp);
         });
       }
-      if (grad_gamma)
-        hipLaunchKernelGGL(rmsnorm_dgamma_part, dim3(n_cb, (unsigned)n_blocks), b, 0, s, (const uint32_t*)x, rstd,
-                           (const float2*)grad_h, T, d, quarters, (float2*)part);
+      if (grad_gamma) {
+        // half a workgroup per CU or fewer: more rows in flight for the chain's latency (1001 rows at d = 2048
+        // 11.3 -> 10.0 us); with more, the loads of the others cover it (10000 at d = 2048 29.7 -> 27.3 with 16)
+        const bool few = 2 * n_blocks * n_cb <= device_cu_count();
+        hipLaunchKernelGGL(few ? rmsnorm_dgamma_part<32> : rmsnorm_dgamma_part<16>, dim3(n_cb, (unsigned)n_blocks), b,
+                           0, s, (const uint16_t*)x, rstd, grad_h, T, d, quarters, part);
+      }
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

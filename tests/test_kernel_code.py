@@ -62,3 +62,14 @@ def test_k_loop_moves_no_accumulators(assembly, shape):
     moves = sum(x.startswith("v_accvgpr") for x in loop)
     print(f"{shape}: {mfma} MFMAs, {moves} accumulator moves, {len(loop)} instructions")
     assert mfma in (32, 64) and moves == 0
+
+
+@pytest.mark.parametrize("kernel,rows", [("rmsnorm_dgamma_partILi16E", 16), ("rmsnorm_dgamma_partILi32E", 32),
+                                         ("rmsnorm_bwd_bothILi8E", 32)])
+def test_column_sums_issue_few_instructions_a_row(assembly, kernel, rows):
+    """grad_gamma's block sums are one chain of rows per workgroup, so a call of few blocks takes its time from the
+    row loop's instructions: a column per thread, `rows` rows' loads ahead, at most 11 a row (two columns took 15)."""
+    loops = [l for l in _loops(assembly("rmsnorm"), kernel) if sum(x == "global_load_ushort" for x in l) == rows]
+    assert loops, "no loop over that many rows' loads"
+    print(f"{kernel}: {len(loops[0])} instructions for {rows} rows")
+    assert len(loops[0]) <= 11 * rows
