@@ -103,4 +103,25 @@ inline StreamShape stream_shape(int64_t rows, int32_t d, int n_ht, int cus) {
   return StreamShape{nb, nb == 2 ? 4 : 8};
 }
 
+// Norm backward at d = 2048 and 4096 with grad_gamma by quarters of 256-row
+// blocks: whether the blocks' sums are taken in the grad_x pass, a workgroup per
+// block. A 256-CU MI355X holds norm_resident of them at once (two per CU at
+// d = 4096, four at 2048) but their time is that of the CUs with the most, so
+// the pass is the faster one where the CUs' last blocks are nearly all there,
+// from 0.8 of them. Against grad_x and the sums over the same rows in one
+// launch, both outputs, us:
+//   d = 4096  65536 rows (256 blocks) 543 and 596, 72000 832 and 662, 90000 909 and 818, 105000 (410 of 512) 956 and
+//             954, 110000 976 and 997, 131071 1101 and 1185
+//   d = 2048  65536 278 and 312, 90000 470 and 424, 105000 486 and 497, 131072 554 and 615, 140000 704 and 657, 160000
+//             (625 of 768) 755 and 751, 196608 841 and 917, 210000 (821 of 1024) 1002 and 985, 250000 1080 and 1164
+// (grad_gamma alone crosses at the same places). From 256 rows per resident
+// block on, the blocks take more rows and always fill the chip.
+inline int64_t norm_resident(int32_t d) { return d == 2048 ? 1024 : 512; }
+inline bool norm_fused(int64_t T, int32_t d) {
+  constexpr int64_t kCUs = 256;
+  if (T >= 256 * norm_resident(d)) return true;
+  const int64_t blocks = (T + 255) / 256, rounds = (blocks + kCUs - 1) / kCUs;
+  return 10 * blocks >= 8 * rounds * kCUs;
+}
+
 }  // namespace tim

@@ -322,10 +322,11 @@ __global__ __launch_bounds__(256) void rmsnorm_dgamma_part(const uint16_t* __res
 // and workgroups of one block's column sums, ordered so that the two run over
 // the same rows at about the same time and x and G come from HBM once, the
 // second read from the memory-side cache. The column sums' workgroups (256 rows
-// in order each, so long ones) go kLead blocks ahead, to end with the others (8
-// and 16 blocks alike; 4 1% and none 2-8% slower). Bound by the cache misses of
-// the XCDs, both reads and the writes (6.8 TB/s): 16384 rows at d = 4096
-// 200 -> 164 us against two launches, of which 114 would be one pass over HBM.
+// in order each, so long ones) go kLead blocks ahead, to end with the others (4
+// and 8 blocks within 2%; 16 4-15% slower from 16384 rows of d = 4096 and 5120
+// on). Bound by the cache misses of the XCDs, both reads and the writes (7.1
+// TB/s): 16384 rows at d = 4096 198 -> 156 us against two launches, of which
+// 114 would be one pass over HBM.
 constexpr int kLead = 8;
 template <int NCL>
 __global__ __launch_bounds__(256) void rmsnorm_bwd_both(const uint4* __restrict__ x, const uint4* __restrict__ gamma,
@@ -419,19 +420,15 @@ hipError_t launch_rmsnorm_backward(const void* x, const void* gamma, const float
                                    int64_t T, int d, float* grad_x, float* grad_gamma, int accumulate, float* part,
                                    hipStream_t s) {
   // From kQuarterRows rows at d = 2048 and 4096 the blocks' sums go by quarters.
-  // With at least 256 rows per resident workgroup (two per CU of a 256-CU
-  // MI355X at d = 4096, four at 2048) they are taken in the grad_x pass, with
-  // or without grad_x: one workgroup per block walks its rows in order and
-  // reads x and G once (138000 rows at d = 4096 with the forward: 1.54 ms, 1.64
-  // as rmsnorm_bwd_both). With fewer rows those blocks leave CUs idle (66000
-  // rows: 0.95 against 0.79 ms). The choice, and so grad_gamma's order, depends
-  // on (T, d) only.
-  const int64_t resident = d == 2048 ? 1024 : 512;
+  // Where norm_fused says so they are taken in the grad_x pass, with or without
+  // grad_x: one workgroup per block walks its rows in order and reads x and G
+  // once. grad_gamma's order depends on (T, d) only, not on this choice.
+  const int64_t resident = norm_resident(d);
   const int quarters = (d == 2048 || d == 4096) && T >= kQuarterRows;
-  const bool fused = grad_gamma && quarters && T >= 256 * resident;
-  // Rows per wave: all the blocks resident at once, none left for a second
-  // round of a few blocks walking their rows alone.
-  const int rpw = (int)((T + 4 * resident - 1) / (4 * resident));
+  const bool fused = grad_gamma && quarters && norm_fused(T, d);
+  // Rows per wave: 64, or more where that many blocks would not all be resident
+  // at once, which would leave a second round of a few blocks walking their rows alone.
+  const int rpw = (int)std::max<int64_t>(64, (T + 4 * resident - 1) / (4 * resident));
   if (fused && T > 0) {
     if ((T + 255) / 256 > 65535) return hipErrorInvalidValue;
     const hipError_t e = d == 2048 ? launch_fused<4>(x, gamma, rstd, grad_h, T, rpw, grad_x, part, s)

@@ -17,6 +17,7 @@ extern "C" int stream_shape(int64_t rows, int d, int n_ht, int cus) {
   const tim::StreamShape s = tim::stream_shape(rows, d, n_ht, cus);
   return 10 * s.row_blocks + s.group;
 }
+extern "C" int norm_fused(int64_t T, int d) { return tim::norm_fused(T, d); }
 """
 
 
@@ -31,6 +32,7 @@ def _lib():
         lib = ctypes.CDLL(so)
     lib.response_blocks.argtypes = [ctypes.c_int] + [ctypes.c_int64] * 3
     lib.stream_shape.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
+    lib.norm_fused.argtypes = [ctypes.c_int64, ctypes.c_int]
     return lib
 
 
@@ -45,3 +47,7 @@ def stream_shape(rows, d, V, cus=256):
     """(row blocks, group) of the wave-per-half kernel for a decode batch, or None for the two-wave tiles."""
     c = _lib().stream_shape(rows, d, -(-V // 128), cus)
     return divmod(c, 10) if c else None
+
+
+def norm_fused(T, d):
+    return bool(_lib().norm_fused(T, d))

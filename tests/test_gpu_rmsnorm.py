@@ -192,14 +192,16 @@ def test_rmsnorm_degenerate_calls():
 
 
 @pytest.mark.parametrize("d,with_gamma,T", [(2048, True, 65536 + 77), (4096, False, 65536 + 77),
+                                            (4096, True, 110000), (2048, True, 131072 - 77),
                                             (4096, True, 131072 + 77), (2048, False, 262144 + 77)])
 def test_rmsnorm_backward_large_call_vs_oracle(d, with_gamma, T):
     """Calls of at least 65536 rows at d = 2048 / 4096 form grad_gamma's block
     sums by quarters (each quarter's rows in order, then (q0 + q1) + (q2 + q3)
-    per block; above 131072 rows at d = 4096, 262144 at d = 2048, the grad_x
-    pass's own waves form them and take more than 64 rows): grad_gamma against the oracle within its bound, grad_x bitwise equal
-    to the same rows evaluated alone (the smaller call's path) and to the
-    oracle on sampled rows, and grad_gamma without grad_x the same bits."""
+    per block), in column sums beside the grad_x pass or in its own waves (here
+    110000 and 130995 rows, and the two largest calls, whose waves take more
+    than 64 rows): grad_gamma against the oracle within its bound, grad_x
+    bitwise equal to the same rows evaluated alone (the smaller call's path) and
+    to the oracle on sampled rows, and grad_gamma without grad_x the same bits."""
     print(f"case large T={T} d={d} gamma={with_gamma}", flush=True)
     x = _x(T, d, d + 7)
     g = _gamma(d, d + 8) if with_gamma else None
