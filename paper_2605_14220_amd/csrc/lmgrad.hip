@@ -378,12 +378,13 @@ static hipError_t launch_small(const GemmArgs& a, hipStream_t s) {
 
 // The output tile of a product and what its rounds over the chip cost: the
 // tiles dealt to the CUs, times one round against a round of 256 x 256 tiles
-// (measured at K = 152064: 3.35 ms; 128 x 256 1.95, 128 x 128 1.25, 64 x 128
-// 0.83, 64 x 64 0.5 ms a round). The smaller the tile the more bytes a CU
-// fetches per flop, so smaller ones only win where larger ones leave CUs idle.
-// grad_hidden at K = 152064: 1001 rows at d = 2048 3.07 ms on 32 tiles of
-// 256 x 256, 0.91 on 256 of 64 x 128; 2000 rows at d = 4096 3.1 ms on 128
-// tiles, 1.95 on 256 of 128 x 256; 3000 rows there stay on 192 tiles of
+// (measured with a tile on every CU at K = 152064: 3.37 ms; 128 x 256 1.95,
+// 128 x 128 1.26, 64 x 128 0.88, 64 x 64 0.60 ms a round; at K = 32000, 8192 and
+// 1024 within a few hundredths of the same ratios). The smaller the tile the
+// more bytes a CU fetches per flop, so smaller ones only win where larger ones
+// leave CUs idle. grad_hidden at K = 152064: 1001 rows at d = 2048 3.05 ms on 32
+// tiles of 256 x 256, 0.89 on 256 of 64 x 128; 2000 rows at d = 4096 2.98 ms on
+// 128 tiles, 2.04 on 256 of 128 x 256; 3000 rows there stay on 192 tiles of
 // 256 x 256 (2 rounds of 128 x 256 cost more).
 struct GemmShape {
   int64_t cost;
@@ -399,8 +400,8 @@ static GemmShape best_shape(int64_t a_rows, int64_t b_rows, int64_t cus) {
   GemmShape best{cost(256, 256, 100), launch_whole};
   for (const GemmShape& c : {GemmShape{cost(128, 256, 58), launch_small<2, 4, 4, 4>},
                              GemmShape{cost(128, 128, 37), launch_small<2, 4, 4, 2>},
-                             GemmShape{cost(64, 128, 24), launch_small<2, 4, 2, 2>},
-                             GemmShape{cost(64, 64, 15), launch_small<2, 2, 2, 2>}})
+                             GemmShape{cost(64, 128, 26), launch_small<2, 4, 2, 2>},
+                             GemmShape{cost(64, 64, 18), launch_small<2, 2, 2, 2>}})
     if (c.cost < best.cost) best = c;
   return best;
 }

@@ -803,13 +803,16 @@ __device__ __forceinline__ void tile_pass_deep(const typename E::Args& a, int n_
 // tile of TA x BT, both dividing 256, so a tile reads a run of whole rows of
 // its operands' packed blocks. One tile per workgroup and one workgroup per CU,
 // its LDS holding as many 64-deep stages as fit, to cover the cache latency of
-// the few KB a stage brings. What bounds it is what one CU fetches: 70-90 GB/s
-// whatever the tile and however many of them run (a stage of 64 x 128 takes
-// 270-300 ns on 64 CUs as on 256, one of 64 x 64 180-190). Eight waves of
-// fewer blocks were faster than four of more (128 x 128: 1.25 against 1.45 ms
-// at K = 152064), which leave one wave per SIMD and nothing to issue while it
-// waits. Refilling a buffer a stage later, without the wait for the reads
-// before the barrier, and other groups of the tile order measured the same.
+// the few KB a stage brings. What bounds it is the CU's own load path: at K =
+// 152064 a CU fetches 57-60 GB/s on 128 x 256 tiles, 61-62 on 128 x 128, 64-67
+// on the two smaller ones with a tile on every CU (up to 70 with fewer, and
+// 75-100 where K is short enough for the caches), with its address units busy
+// 96% of the time (64 x 128 tiles of 1001 rows at d = 2048; 92% for 128 x 128)
+// and the MFMAs 36% (47%). Eight waves of fewer blocks were faster than four of
+// more (128 x 128: 1.25 against 1.45 ms at K = 152064), which leave one wave per
+// SIMD and nothing to issue while it waits. Refilling a buffer a stage later,
+// without the wait for the reads before the barrier, and other groups of the
+// tile order measured the same.
 template <int NV, int WT, int NA, int NB>
 struct SmallTile {
   static constexpr int NW = NV * WT;
