@@ -130,9 +130,13 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# The current stream's handle alone: building the Stream object of torch.cuda.current_stream takes 2 us of every call.
+# The name is private to torch, so a version without it takes the public call.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device) -> int:
-    # the handle alone: building the Stream object of torch.cuda.current_stream takes 2 us of every call
-    return torch._C._cuda_getCurrentRawStream(device.index)
+    return torch.cuda.current_stream(device).cuda_stream if _raw_stream is None else _raw_stream(device.index)
 
 
 def _require_gpu(*tensors):

@@ -340,6 +340,18 @@ def test_python_binding_rejects_cpu_tensors():
         tim.mismatch(torch.zeros(3), torch.zeros(3))
 
 
+def test_stream_handle_without_the_private_call(monkeypatch):
+    """The binding's stream is torch's current one, through the public call where torch has no raw handle."""
+    import types
+
+    import torch
+    monkeypatch.setattr(tim, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda d: types.SimpleNamespace(cuda_stream=7 + d.index))
+    assert tim._stream(torch.device("cuda", 1)) == 8
+    monkeypatch.setattr(tim, "_raw_stream", lambda i: 30 + i)
+    assert tim._stream(torch.device("cuda", 2)) == 32
+
+
 # ---------------------------------------------------------------- backward
 
 def _bwd_size(T, d, V, mb):
